@@ -13,11 +13,8 @@
 #include "common.h"
 #include "kernels.h"
 
-// site slabs (64 sites) per weight-gradient chunk, 128- and 64-wide tiles
-#ifndef WG_SLABS_128
-#define WG_SLABS_128 8
-#define WG_SLABS_64 12
-#endif
+// site slabs (64 sites, 32 for float32) per weight-gradient chunk, 128- and 64-wide tiles
+constexpr int WG_SLABS_128 = 8, WG_SLABS_64 = 12;
 
 using namespace sscn;
 
@@ -196,7 +193,7 @@ static int64_t route_tiles(const sscn_net* net, int s, int* bm) {
   const LayerPlan& Lp = net->L[s - 1];
   if (L.kind != 1 || Lp.kind != 2 || net->L[s - 2].kind != 1 || L.A < 2) return 0;
   const ParamPlan& P = net->P[L.conv_index];
-  if (P.pd.ksplit != 1 || !gemm_routes(net->bf16, P.pd.cfg)) return 0;
+  if (P.pd.ksplit != 1) return 0;
   *bm = gemm_bm(net->bf16, P.pd.cfg);
   return (Lp.cap + *bm - 1) / *bm;  // rows 1 .. cap
 }
@@ -280,7 +277,11 @@ static void carve(sscn_net* net, void* base) {
   net->ws_bytes = cv.off + 256;
 }
 
-static void set_plan(GemmArgs& g, const GemmPlan& p, int64_t rows_cap, float* gpart) {
+// 16 zero bytes in the workspace: the input's ground row, which every forward pass writes.
+static const void* zeros(const sscn_net* net) { return net->L[0].X; }
+
+static void set_plan(const sscn_net* net, GemmArgs& g, const GemmPlan& p, int64_t rows_cap, float* gpart) {
+  g.zero = zeros(net);
   g.cfg = p.cfg;
   g.sk = p.sk;
   g.ksplit = p.ksplit;
@@ -339,8 +340,6 @@ sscn_status sscn_net_create(const sscn_net_desc* desc, sscn_net** out) {
   net->nconv = nin ? 2 * d.ell + 2 : d.ell + 1;
   net->nparams = net->nconv + 1;
   net->pool_parts = 1024;  // most row blocks per slot of a bias / ground-row reduction
-  net->wgrad_slabs[0] = WG_SLABS_128;
-  net->wgrad_slabs[1] = WG_SLABS_64;
   const int BK = net->bf16 ? 64 : 32;
   const int VE = net->VE;
   auto cp = [VE](int c) { return (int)round_up(c, VE); };
@@ -443,12 +442,25 @@ sscn_status sscn_net_create(const sscn_net_desc* desc, sscn_net** out) {
     P.Mpad_w = (int)round_up(P.A * P.cp_in, WG_BM);
     P.bn_w = wgrad_bn(P.c_out);
     P.Npad_w = (int)round_up(P.c_out, P.bn_w);
-    {
-      const int m_rows = P.A * P.cp_in;
+  }
+  // Site chunks of the weight gradients: 8 slabs of sites each (128-wide tiles)
+  // or 12 (64-wide), and a half or a quarter of that while the convolutions' tiles
+  // at the row bound number fewer than 1024: a small network's few chunks would
+  // each be a long serial loop on a mostly idle chip (DeepCNet(4,20), float32,
+  // batch 8: 88 tiles, 41 us; bf16, batch 100: 372 tiles, 32 us).
+  for (int div = 1; div <= 4; div *= 2) {
+    net->wgrad_slabs[0] = WG_SLABS_128 / div;
+    net->wgrad_slabs[1] = WG_SLABS_64 / div;
+    int64_t tiles = 0;
+    for (int s = 1; s < net->nlayers; ++s) {
+      if (L[s].kind != 1) continue;
+      ParamPlan& P = net->P[L[s].conv_index];
       const int64_t row_bytes = (int64_t)(P.A * P.cp_in + P.cp_out) * net->esz;
-      const int64_t part_bytes = (int64_t)m_rows * P.Npad_w * 4;
+      const int64_t part_bytes = (int64_t)P.A * P.cp_in * P.Npad_w * 4;
       P.nchunks = wgrad_chunks(L[s].cap + 1, net->wgrad_slabs[P.bn_w == 128 ? 0 : 1], BK, row_bytes, part_bytes);
+      tiles += (int64_t)P.nchunks * (P.Mpad_w / WG_BM) * (P.Npad_w / P.bn_w);
     }
+    if (tiles >= 1024) break;
   }
   {
     ParamPlan& P = net->P[net->nconv];
@@ -646,7 +658,7 @@ static bool pool_fused(const sscn_net* net, int s) {
   const LayerPlan& Lp = net->L[s + 1];
   if (L.kind != 1 || Lp.kind != 2 || L.S % 2 != 0 || Lp.Cp != L.Cp) return false;
   const ParamPlan& P = net->P[L.conv_index];
-  return P.pf.ksplit == 1 && gemm_routes(net->bf16, P.pf.cfg);
+  return P.pf.ksplit == 1;
 }
 
 // Stage s of the forward pass; with fuse_pool a convolution whose pooling
@@ -684,7 +696,7 @@ static hipError_t forward_stage(sscn_net* net, int s, hipStream_t st, bool fuse_
     g.rows_dev = net->counts + s;
     g.rows_add = 1;
     g.row_begin = 0;
-    set_plan(g, P.pf, P.rows_f, net->gpart);
+    set_plan(net, g, P.pf, P.rows_f, net->gpart);
     int64_t max_rows = L.cap + 1;
     if (fuse_pool && pool_fused(net, s)) {  // rows: the four slots of every pooling window
       const LayerPlan& Lp = net->L[s + 1];
@@ -827,6 +839,7 @@ static WGradArgs conv_wgrad_args(const sscn_net* net, int s) {
   const ParamPlan& P = net->P[ci];
   WGradArgs w{};
   w.src = conv_drop(net, s).on ? Lb.Xd : Lb.X;  // the input the forward pass used
+  w.zero = zeros(net);
   w.src_stride = Lb.Cp;
   w.rmap = L.rules;
   w.A = L.A;
@@ -959,7 +972,7 @@ static hipError_t rows_below(sscn_net* net, int s, hipStream_t st, const ExtraTa
     g.rmap = nullptr;
     g.row_begin = 0;
   }
-  set_plan(g, P.pd, P.rows_d, net->gpart);
+  set_plan(net, g, P.pd, P.rows_d, net->gpart);
   int rac = 0, rbm = 0, rtiles = 0;
   if (allow_route && route_into(net, s, &rac, &rbm, &rtiles)) {
     g.route = 1;
@@ -1038,7 +1051,7 @@ sscn_status sscn_forward(sscn_net* net, const void* d_feats, const void* const* 
   g.epi = EPI_BIAS_F32;
   g.rows_host = net->batch;
   g.row_begin = 0;
-  set_plan(g, P.pf, P.rows_f, net->gpart);
+  set_plan(net, g, P.pf, P.rows_f, net->gpart);
   net->forwarded = false;
   if (timed_gemm(net, g, net->batch, st, 0, SSCN_ROLE_SOFTMAX_FWD) != hipSuccess)
     return SSCN_ERR_HIP;
@@ -1085,7 +1098,7 @@ sscn_status sscn_backward(sscn_net* net, float* const* h_dW, float* const* h_db,
   g.epi = EPI_F32;
   g.rows_host = net->batch;
   g.row_begin = 0;
-  set_plan(g, P.pd, P.rows_d, net->gpart);
+  set_plan(net, g, P.pd, P.rows_d, net->gpart);
   g.partials_only = g.ksplit > 1;  // the head backward sums the split-K partials itself
   if (timed_gemm(net, g, net->batch, st, 0, SSCN_ROLE_SOFTMAX_DH) != hipSuccess)
     return SSCN_ERR_HIP;
@@ -1210,6 +1223,7 @@ sscn_status sscn_backward(sscn_net* net, float* const* h_dW, float* const* h_db,
     f = WGradArgs{};
     const bool hd = head_drop(net).on;  // the softmax layer read its dropped input
     f.src = hd ? net->hdrop : Lt.X;
+    f.zero = zeros(net);
     f.src_stride = Lt.Cp;
     f.rmap = hd ? nullptr : net->head_rows;
     f.A = 1;

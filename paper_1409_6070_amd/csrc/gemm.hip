@@ -43,15 +43,7 @@ struct MfmaCore<__bf16> {
 
 template <>
 struct MfmaCore<float> {
-  static constexpr int KB = 16;
-  __device__ static inline void step(const float* a_ptr, const float* b_ptr, f32x4& acc) {
-    f32x4 a = *(const f32x4*)a_ptr;
-    f32x4 b = *(const f32x4*)b_ptr;
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0], b[0], acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[1], b[1], acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[2], b[2], acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[3], b[3], acc, 0, 0, 0);
-  }
+  static constexpr int KB = 16;  // four 16x16x4 steps: step e takes k = 4 g + e of lane group g on both sides
 };
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -67,34 +59,27 @@ struct GCfg {
   static constexpr int KB = MfmaCore<T>::KB;
   static constexpr int BK = 2 * KB;
   static constexpr int KV = BK / VE;       // 16-byte vectors per row and slab
-  static constexpr int LDK = BK + VE;      // LDS row pitch (elements), padded against bank conflicts
   static constexpr int AV = BM * KV / NT;  // A vectors per thread and slab
   static constexpr int BV = BN * KV / NT;
   static_assert(AV * NT == BM * KV && BV * NT == BN * KV, "tile must split evenly over the threads");
+  // first column of the tile that wave column wn's block j computes: the waves'
+  // blocks interleave, so that where the columns end inside a tile its waves
+  // are left with equal numbers of live blocks
+  __device__ static inline int col(int wn, int j) { return (j * WN + wn) * 16; }
+  // the weight gradients' rows likewise
+  __device__ static inline int row(int wm, int i) { return (i * WM + wm) * 16; }
 };
 
 constexpr int AMAX = 9;  // largest window (3x3)
 
 // the four tile shapes (index = GemmArgs::cfg)
-template <typename T> using C128x128 = GCfg<T, 2, 2, 4, 4>;
+// (bf16 multiplies square wave tiles, whose operands take the fewest LDS reads;
+// float32, whose MFMAs outlast them, gives every wave whole rows, so that dead
+// column blocks leave all waves alike)
+template <typename T> using C128x128 = GCfg<T, sizeof(T) == 2 ? 2 : 4, sizeof(T) == 2 ? 2 : 1, sizeof(T) == 2 ? 4 : 2, sizeof(T) == 2 ? 4 : 8>;
 template <typename T> using C128x64 = GCfg<T, 4, 1, 2, 4>;
-template <typename T> using C64x64 = GCfg<T, 2, 2, 2, 2>;
+template <typename T> using C64x64 = GCfg<T, sizeof(T) == 2 ? 2 : 4, sizeof(T) == 2 ? 2 : 1, sizeof(T) == 2 ? 2 : 1, sizeof(T) == 2 ? 2 : 4>;
 template <typename T> using C32x64 = GCfg<T, 2, 2, 1, 2>;
-
-template <class C>
-constexpr bool stages_tile() {
-  return C::BM * (C::BN + C::VE) <= (C::BM + C::BN) * C::LDK;
-}
-
-bool gemm_routes(bool bf16, int cfg) {
-  if (cfg == GEMM_DIRECT) return bf16;
-  switch (cfg) {
-    case 0: return bf16 ? stages_tile<C128x128<__bf16>>() : stages_tile<C128x128<float>>();
-    case 1: return bf16 ? stages_tile<C128x64<__bf16>>() : stages_tile<C128x64<float>>();
-    case 2: return bf16 ? stages_tile<C64x64<__bf16>>() : stages_tile<C64x64<float>>();
-    default: return bf16 ? stages_tile<C32x64<__bf16>>() : stages_tile<C32x64<float>>();
-  }
-}
 
 int gemm_bm(bool bf16, int cfg) { return cfg == GEMM_DIRECT ? DIRECT_BM : gemm_tile(bf16, cfg).BM; }
 
@@ -108,41 +93,59 @@ GemmTile gemm_tile(bool bf16, int cfg) {
   }
 }
 
-// acc[i][j] += A_tile(wave rows i) * B_tile(wave cols j) over one slab in LDS
-template <typename T, class C>
+// acc[i][j] += A_tile(wave rows i) * B_tile(wave column blocks j) over one slab
+// held in LDS unpadded and swizzled: row r's 16-byte chunk c sits in slot
+// c ^ ((r / 2) % 8) of its 128-byte row, so the sixteen rows an MFMA operand
+// read touches cover all 64 banks once.  Only the wave's first LIVE column
+// blocks are computed.
+template <typename T, class C, int LIVE>
 __device__ inline void mma_slab(const T* As, const T* Bs, f32x4 (&acc)[C::TM][C::TN], int wm, int wn, int lane) {
+  constexpr int VE = C::VE;
   const int r16 = lane & 15, g = lane >> 4;
+  auto a_at = [&](int i, int chunk) {
+    const int r = wm * C::TM * 16 + i * 16 + r16;
+    return As + r * C::BK + ((chunk ^ ((r >> 1) & 7)) * VE);
+  };
+  auto b_at = [&](int j, int chunk) {
+    const int r = C::col(wn, j) + r16;
+    return Bs + r * C::BK + ((chunk ^ ((r >> 1) & 7)) * VE);
+  };
 #pragma unroll
   for (int kb = 0; kb < C::BK; kb += C::KB) {
+    const int chunk = kb / VE + g;
+    if constexpr (sizeof(T) == 2) {
 #pragma unroll
-    for (int i = 0; i < C::TM; ++i)
+      for (int i = 0; i < C::TM; ++i)
 #pragma unroll
-      for (int j = 0; j < C::TN; ++j)
-        MfmaCore<T>::step(As + (wm * C::TM * 16 + i * 16 + r16) * C::LDK + kb + g * C::VE,
-                          Bs + (wn * C::TN * 16 + j * 16 + r16) * C::LDK + kb + g * C::VE, acc[i][j]);
+        for (int j = 0; j < LIVE; ++j) MfmaCore<T>::step(a_at(i, chunk), b_at(j, chunk), acc[i][j]);
+    } else {
+      f32x4 av[C::TM], bv[LIVE];
+#pragma unroll
+      for (int i = 0; i < C::TM; ++i) av[i] = *(const f32x4*)a_at(i, chunk);
+#pragma unroll
+      for (int j = 0; j < LIVE; ++j) bv[j] = *(const f32x4*)b_at(j, chunk);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int j = 0; j < LIVE; ++j)
+#pragma unroll
+          for (int i = 0; i < C::TM; ++i)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i][e], bv[j][e], acc[i][j], 0, 0, 0);
+    }
   }
 }
 
-// acc += A_tile * B_tile over one slab held in LDS unpadded and swizzled (the
-// bf16 pipeline below): row r's 16-byte chunk c sits in slot c ^ ((r / 2) % 8)
-// of its 128-byte row, so the sixteen rows an MFMA operand read touches cover
-// all 64 banks once.
-template <class C>
-__device__ inline void mma_slab_sw(const __bf16* As, const __bf16* Bs, f32x4 (&acc)[C::TM][C::TN], int wm, int wn,
-                                   int lane) {
-  const int r16 = lane & 15, g = lane >> 4;
-#pragma unroll
-  for (int kb = 0; kb < C::BK; kb += C::KB) {
-    const int chunk = kb / 8 + g;
-#pragma unroll
-    for (int i = 0; i < C::TM; ++i)
-#pragma unroll
-      for (int j = 0; j < C::TN; ++j) {
-        const int ra = wm * C::TM * 16 + i * 16 + r16, rb = wn * C::TN * 16 + j * 16 + r16;
-        MfmaCore<__bf16>::step(As + ra * C::BK + ((chunk ^ ((ra >> 1) & 7)) * 8),
-                               Bs + rb * C::BK + ((chunk ^ ((rb >> 1) & 7)) * 8), acc[i][j]);
-      }
+// Calls run(integral_constant<int, N>) with the smallest N in [LO, HI] that is at
+// least n (HI when none is).
+template <int LO, int HI, class F>
+__device__ inline void with_count(int n, F&& run) {
+  if constexpr (LO < HI) {
+    if (n > LO) {
+      with_count<LO + 1, HI>(n, run);
+      return;
+    }
   }
+  run(std::integral_constant<int, LO>{});
 }
 
 // s_waitcnt vmcnt(n) lgkmcnt(0), n a compile-time constant: the LDS reads of
@@ -179,6 +182,26 @@ __device__ inline void dma4(u32x4 rsrc, uint32_t lds, uint32_t off) {
       : "m0");
 }
 
+// The same two loads from a 64-bit address per lane (float32: its feature
+// arrays may pass the 2 GiB that a buffer's offsets reach; a lane without a
+// source reads zeros from an address that holds them).
+__device__ inline void dma16_at(uint32_t lds, const void* p) {
+  asm volatile(
+      "s_mov_b32 m0, %0\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %1, off" ::"s"(lds),
+      "v"(p)
+      : "m0");
+}
+__device__ inline void dma4_at(uint32_t lds, const void* p) {
+  asm volatile(
+      "s_mov_b32 m0, %0\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dword %1, off" ::"s"(lds),
+      "v"(p)
+      : "m0");
+}
+
 // raw buffer descriptor: base, no stride, size in bytes
 __device__ inline u32x4 buffer_rsrc(const void* base, uint32_t bytes) {
   const uint64_t b = (uint64_t)base;
@@ -198,13 +221,14 @@ __device__ inline int div_small(int k, int d, float rcp) {
 }
 
 // Routing inputs of the items a thread takes in store_staged (AC >= 0 and at
-// most two items per thread), all loaded before the first item is routed: one
-// memory round trip for the thread's items, not one each.
+// most two items per thread, four of float32's half as wide ones), all loaded
+// before the first item is routed: one memory round trip for the thread's
+// items, not one each.
 template <typename T, class C, int AC>
 struct StagedRoute {
   static constexpr int NV = C::BN / C::VE;
   static constexpr int IPT = (C::BM * NV + C::NT - 1) / C::NT;  // items per thread
-  static constexpr bool ON = AC >= 0 && IPT <= 2;
+  static constexpr bool ON = AC >= 0 && IPT <= (sizeof(T) == 2 ? 2 : 4);
   RouteIn<T, AC < 0 ? 0 : AC> q[ON ? IPT : 1];
   __device__ inline void load(const GemmArgs& a, int m0, int n0, int rows) {
     if constexpr (ON) {
@@ -221,8 +245,8 @@ struct StagedRoute {
 
 // Stores of an output tile staged in LDS (Cs, pitch CS), 16 bytes at a time.
 // AC >= 0: the pooling backward of every row m >= 1 as well, and the tile's
-// slot partial sums as partial tm (lds: the staging buffer, reused).
-template <typename T, class C, int CS, int AC>
+// slot partial sums as partial tm (lds: the staging buffer, reused; LDSF floats).
+template <typename T, class C, int CS, int AC, int LDSF>
 __device__ inline void store_staged(const GemmArgs& a, const T* Cs, int m0, int n0, int tm, int rows, float* lds) {
   constexpr int VE = C::VE, BM = C::BM, BN = C::BN, NT = C::NT, NV = BN / VE;
   constexpr int J = AC >= 0 ? 2 + AC : 1;
@@ -263,7 +287,7 @@ __device__ inline void store_staged(const GemmArgs& a, const T* Cs, int m0, int 
       }
     }
   }
-  if constexpr (AC >= 0) tile_slot_sums<VE, J, NT, NV, (BM + BN) * C::LDK * (int)sizeof(T) / 4>(acc, lds, a.pr, n0, tm);
+  if constexpr (AC >= 0) tile_slot_sums<VE, J, NT, NV, LDSF>(acc, lds, a.pr, n0, tm);
 }
 
 // Pooling forward in the epilogue (GemmArgs::pool_fwd): the staged tile's
@@ -309,36 +333,29 @@ __device__ inline void store_pooled(const GemmArgs& a, const T* Cs, const int32_
 }
 
 // Implicit-gather GEMM.  Per tile: the tile's window rows go to LDS once; the
-// K slabs stream through a ring of LDS stages filled by buffer loads with an
-// LDS destination (bf16; float32 prefetches the next slab into registers);
-// the output tile is staged in LDS for 16-byte stores.
+// K slabs stream through a ring of LDS stages filled by loads with an LDS
+// destination (bf16: buffer loads, an offset past the buffer reads zero;
+// float32: loads from 64-bit addresses); the output tile is staged in LDS for
+// 16-byte stores.
 // With ksplit > 1 each workgroup covers one K range and writes fp32 partial
 // sums, reduced (with the epilogue) by k_gemm_splitk_reduce.
 template <typename T, class C, int RAC>
 __global__ void __launch_bounds__(C::NT) k_gemm_gather(GemmArgs a) {
-  constexpr int VE = C::VE, BK = C::BK, KV = C::KV, LDK = C::LDK, BM = C::BM, BN = C::BN, NT = C::NT;
-  constexpr int SMEM = (BM + BN) * LDK;
+  constexpr int VE = C::VE, BK = C::BK, BM = C::BM, BN = C::BN, NT = C::NT;
   constexpr int CS = BN + VE;  // staging pitch
-  constexpr bool STAGE = stages_tile<C>();
-  static_assert(STAGE == (BM * CS <= SMEM), "staging fits");
   constexpr bool POOL = RAC == POOL_FWD_MODE;
-  // bf16: the operands go from memory straight into LDS (buffer loads with an
-  // LDS destination; an offset past the buffer reads zero), NST slabs in LDS,
-  // NST - 1 of them in flight while one is multiplied, one barrier per slab.
-  // Two stages where three would cost occupancy (the 128x128 tile; the pooled
-  // forward, which then fits three workgroups per compute unit and its
-  // launches one round of workgroups) or measured slower (the routed tiles,
-  // whose epilogue holds more registers).
-  constexpr bool DMA = sizeof(T) == 2;
-  constexpr int NST = (BM + BN >= 256 || RAC >= 0 || POOL) ? 2 : 3;
+  // NST slabs in LDS, NST - 1 of them in flight while one is multiplied, one
+  // barrier per slab.  Two stages where three would cost occupancy (the 128x128
+  // tile; the pooled forward, which then fits three workgroups per compute unit
+  // and its launches one round of workgroups) or measured slower (the routed
+  // tiles, whose epilogue holds more registers).
+  constexpr int NST = (BM + BN >= 256 || (sizeof(T) == 2 && (RAC >= 0 || POOL))) ? 2 : 3;
   constexpr int STG = (BM + BN) * BK;          // elements per stage
   constexpr int LPS = C::AV + C::BV;           // loads per thread and slab
-  constexpr int SMEM_ALL = DMA ? (NST * STG > SMEM ? NST * STG : SMEM) : SMEM;
-  __shared__ __attribute__((aligned(16))) T smem[SMEM_ALL];
+  constexpr int SMEM = NST * STG > BM * CS ? NST * STG : BM * CS;
+  __shared__ __attribute__((aligned(16))) T smem[SMEM];
   extern __shared__ int32_t Rs[];  // [BM * A] window entries, sized at launch
   __shared__ int32_t Cr[POOL ? BM : 1];  // pooling forward: the convolution row of each slot
-  T* As = smem;
-  T* Bs = smem + BM * LDK;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
@@ -397,107 +414,102 @@ __global__ void __launch_bounds__(C::NT) k_gemm_gather(GemmArgs a) {
       for (int j = 0; j < C::TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     const float rcp_cseg = 1.f / (float)a.cseg;
-    if constexpr (DMA) {
+    // this wave's column blocks below the result's width
+    const int live =
+        __builtin_amdgcn_readfirstlane((min(a.out_cols - n0, BN) - wn * 16 + 16 * C::WN - 1) / (16 * C::WN));
+    {
       // A: one 16-byte slot per load (row v / 8, slot v % 8 holding chunk
       // (v % 8) ^ ((row / 2) % 8)); rows without a window entry and k past K read zero
       const u32x4 rsA = buffer_rsrc(src, GATHER_SRC_BYTES);
       const u32x4 rsB = buffer_rsrc(Bt, (uint32_t)a.Npad * (uint32_t)a.Kpad * 2u);
       const int wave_u = __builtin_amdgcn_readfirstlane(wave);  // in a scalar register
       const uint32_t lds0 = lds_addr(smem);
+      const uint32_t row_bytes = (uint32_t)a.src_stride * (uint32_t)sizeof(T);
       auto issue = [&](int k0, int st) {
-        const uint32_t la = lds0 + (uint32_t)(st * STG) * 2u, lb = la + BM * BK * 2;
-        uint32_t off[C::AV];
+        const uint32_t la = lds0 + (uint32_t)(st * STG * (int)sizeof(T)), lb = la + BM * BK * (int)sizeof(T);
+        if constexpr (sizeof(T) == 2) {
+          uint32_t off[C::AV];
 #pragma unroll
-        for (int j = 0; j < C::AV; ++j) {  // every window row read before the first load goes out
-          const int v = tid + j * NT;
-          const int r = v >> 3, c = (v & 7) ^ ((r >> 1) & 7);
-          const int k = k0 + c * 8;
+          for (int j = 0; j < C::AV; ++j) {  // every window row read before the first load goes out
+            const int v = tid + j * NT;
+            const int r = v >> 3, c = (v & 7) ^ ((r >> 1) & 7);
+            const int k = k0 + c * VE;
+            const bool in_k = k < a.K;
+            const int f = div_small(k, a.cseg, rcp_cseg);
+            const int srow = Rs[r * A + (in_k ? f : 0)];
+            off[j] = in_k && srow >= 0 ? (uint32_t)(srow * a.src_stride + (k - f * a.cseg)) * 2u : GATHER_SRC_BYTES;
+          }
+#pragma unroll
+          for (int j = 0; j < C::AV; ++j) dma16(rsA, la + (uint32_t)(wave_u * 64 + j * NT) * 16u, off[j]);
+#pragma unroll
+          for (int j = 0; j < C::BV; ++j) {
+            const int v = tid + j * NT;
+            const int r = v >> 3, c = (v & 7) ^ ((r >> 1) & 7);
+            dma16(rsB, lb + (uint32_t)(wave_u * 64 + j * NT) * 16u, (uint32_t)((n0 + r) * a.Kpad + k0 + c * VE) * 2u);
+          }
+        } else {
+          // (every slot of a thread holds the same chunk: one window position
+          // and channel per slab; selects, no branches)
+          const int c = (tid & 7) ^ ((tid >> 4) & 7), k = k0 + c * VE;
+          static_assert(NT == 256, "rows 32 apart share their swizzle");
           const bool in_k = k < a.K;
           const int f = div_small(k, a.cseg, rcp_cseg);
-          const int srow = Rs[r * A + (in_k ? f : 0)];
-          off[j] = in_k && srow >= 0 ? (uint32_t)(srow * a.src_stride + (k - f * a.cseg)) * 2u : GATHER_SRC_BYTES;
-        }
+          const T* col = src + (k - f * a.cseg);
+          const int32_t* R = Rs + (tid >> 3) * A + (in_k ? f : 0);
+          int srow[C::AV];
 #pragma unroll
-        for (int j = 0; j < C::AV; ++j) dma16(rsA, la + (uint32_t)(wave_u * 64 + j * NT) * 16u, off[j]);
+          for (int j = 0; j < C::AV; ++j) srow[j] = R[j * (NT / 8) * A];
 #pragma unroll
-        for (int j = 0; j < C::BV; ++j) {
-          const int v = tid + j * NT;
-          const int r = v >> 3, c = (v & 7) ^ ((r >> 1) & 7);
-          dma16(rsB, lb + (uint32_t)(wave_u * 64 + j * NT) * 16u, (uint32_t)((n0 + r) * a.Kpad + k0 + c * 8) * 2u);
+          for (int j = 0; j < C::AV; ++j) {
+            const uint64_t at = (uint64_t)col + (uint64_t)(uint32_t)srow[j] * row_bytes;
+            dma16_at(la + (uint32_t)(wave_u * 64 + j * NT) * 16u,
+                     (const void*)(in_k && srow[j] >= 0 ? at : (uint64_t)a.zero));
+          }
+          const T* bcol = Bt + ((int64_t)(n0 + (tid >> 3)) * a.Kpad + k);
+#pragma unroll
+          for (int j = 0; j < C::BV; ++j)
+            dma16_at(lb + (uint32_t)(wave_u * 64 + j * NT) * 16u, bcol + (int64_t)j * (NT / 8) * a.Kpad);
         }
       };
-      const int nsl = (kend - kbeg) / BK;
+      const int nsl = kend > kbeg ? (kend - kbeg) / BK : 0;  // (a K range may be empty: its sums are zero)
 #pragma unroll
       for (int p = 0; p < NST - 1; ++p)
         if (p < nsl) issue(kbeg + p * BK, p);
-      for (int s = 0; s < nsl; ++s) {
-        // this wave's loads of slab s have landed once at most those of the
-        // slabs after it are outstanding; the barrier makes it every wave's
-        asm volatile("" ::: "memory");
-        if constexpr (NST == 3) {
-          if (s + 1 < nsl) wait_vmcnt<LPS>(); else wait_vmcnt<0>();
-        } else {
-          wait_vmcnt<0>();
-        }
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        if (s + NST - 1 < nsl) issue(kbeg + (s + NST - 1) * BK, (s + NST - 1) % NST);
-        mma_slab_sw<C>(smem + (s % NST) * STG, smem + (s % NST) * STG + BM * BK, acc, wm, wn, lane);
-      }
-      asm volatile("" ::: "memory");
-      __syncthreads();  // every wave done with the slabs before the epilogue reuses the memory
-    } else {
-      u32x4 ra[C::AV], rb[C::BV];
-      auto load = [&](int k0) {
-        int srow[C::AV], col[C::AV];
-#pragma unroll
-        for (int j = 0; j < C::AV; ++j) {  // window row and channel of each vector, then all loads at once
-          const int v = tid + j * NT;
-          const int r = v / KV, kv = v - r * KV;
-          const int k = k0 + kv * VE;
-          const bool in_k = k < a.K;
-          const int f = in_k ? div_small(k, a.cseg, rcp_cseg) : 0;
-          srow[j] = in_k ? Rs[r * A + f] : -1;
-          col[j] = in_k ? k - f * a.cseg : 0;
-        }
-#pragma unroll
-        for (int j = 0; j < C::AV; ++j) {
-          const u32x4 val = *(const u32x4*)(src + (int64_t)max(srow[j], 0) * a.src_stride + col[j]);
-          ra[j] = srow[j] >= 0 ? val : u32x4{0u, 0u, 0u, 0u};
-        }
-#pragma unroll
-        for (int j = 0; j < C::BV; ++j) {
-          const int v = tid + j * NT;
-          const int r = v / KV, kv = v - r * KV;
-          rb[j] = *(const u32x4*)(Bt + (int64_t)(n0 + r) * a.Kpad + k0 + kv * VE);
+      auto slab_loop = [&](auto live_c) {
+        constexpr int LIVE = decltype(live_c)::value;
+        for (int s = 0; s < nsl; ++s) {
+          // this wave's loads of slab s have landed once at most those of the
+          // slabs after it are outstanding; the barrier makes it every wave's
+          asm volatile("" ::: "memory");
+          if constexpr (NST == 3) {
+            if (s + 1 < nsl) wait_vmcnt<LPS>(); else wait_vmcnt<0>();
+          } else {
+            wait_vmcnt<0>();
+          }
+          __builtin_amdgcn_s_barrier();
+          asm volatile("" ::: "memory");
+          if (s + NST - 1 < nsl) issue(kbeg + (s + NST - 1) * BK, (s + NST - 1) % NST);
+          mma_slab<T, C, LIVE>(smem + (s % NST) * STG, smem + (s % NST) * STG + BM * BK, acc, wm, wn, lane);
         }
       };
-      if (kbeg < kend) load(kbeg);
-      for (int k0 = kbeg; k0 < kend; k0 += BK) {
-#pragma unroll
-        for (int j = 0; j < C::AV; ++j) {
-          const int v = tid + j * NT;
-          const int r = v / KV, kv = v - r * KV;
-          *(u32x4*)(As + r * LDK + kv * VE) = ra[j];
-        }
-#pragma unroll
-        for (int j = 0; j < C::BV; ++j) {
-          const int v = tid + j * NT;
-          const int r = v / KV, kv = v - r * KV;
-          *(u32x4*)(Bs + r * LDK + kv * VE) = rb[j];
-        }
-        __syncthreads();
-        if (k0 + BK < kend) load(k0 + BK);
-        mma_slab<T, C>(As, Bs, acc, wm, wn, lane);
-        __syncthreads();
-      }
+      // float32: column blocks past the result's width are not multiplied (a
+      // block costs TM x 4 MFMAs of 32 cycles per 16 k), with a copy of the loop
+      // for each count (branches around the MFMAs cost more than they save: the
+      // 64 x 64 tile's input gradients 39 -> 59 us); bf16 multiplies them all.
+      // (Every wave passes the same barriers in whichever copy it runs.)
+      if constexpr (sizeof(T) == 2)
+        slab_loop(std::integral_constant<int, C::TN>{});
+      else
+        with_count<C::TN == 8 ? 5 : 1, C::TN>(live, slab_loop);
+      asm volatile("" ::: "memory");
+      __syncthreads();  // every wave done with the slabs before the epilogue reuses the memory
     }
 
     const int g = lane >> 4, c16 = lane & 15;
     float bias[C::TN];
 #pragma unroll
     for (int j = 0; j < C::TN; ++j) {
-      const int n = n0 + wn * C::TN * 16 + j * 16 + c16;
+      const int n = n0 + C::col(wn, j) + c16;
       bias[j] = (a.bias && n < a.N) ? a.bias[n] : 0.f;
     }
     if (a.ksplit > 1) {
@@ -506,20 +518,20 @@ __global__ void __launch_bounds__(C::NT) k_gemm_gather(GemmArgs a) {
       for (int i = 0; i < C::TM; ++i)
 #pragma unroll
         for (int j = 0; j < C::TN; ++j) {
-          const int n = n0 + wn * C::TN * 16 + j * 16 + c16;
+          const int n = n0 + C::col(wn, j) + c16;
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             const int m = m0 + wm * C::TM * 16 + i * 16 + g * 4 + r;
             if (m < rows) part[(int64_t)m * a.Npad + n] = acc[i][j][r];
           }
         }
-    } else if (STAGE && epi_stores_T(a.epi)) {
+    } else if (epi_stores_T(a.epi)) {
       T* Cs = smem;
 #pragma unroll
       for (int i = 0; i < C::TM; ++i)
 #pragma unroll
         for (int j = 0; j < C::TN; ++j) {
-          const int nl = wn * C::TN * 16 + j * 16 + c16;
+          const int nl = C::col(wn, j) + c16;
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             const int ml = wm * C::TM * 16 + i * 16 + g * 4 + r;
@@ -535,13 +547,13 @@ __global__ void __launch_bounds__(C::NT) k_gemm_gather(GemmArgs a) {
       if constexpr (POOL)
         store_pooled<T, C, CS>(a, Cs, Cr, m0, n0, rows);
       else
-        store_staged<T, C, CS, RAC>(a, Cs, m0, n0, tm, rows, (float*)smem);
+        store_staged<T, C, CS, RAC, SMEM * (int)sizeof(T) / 4>(a, Cs, m0, n0, tm, rows, (float*)smem);
     } else {
 #pragma unroll
       for (int i = 0; i < C::TM; ++i)
 #pragma unroll
         for (int j = 0; j < C::TN; ++j) {
-          const int n = n0 + wn * C::TN * 16 + j * 16 + c16;
+          const int n = n0 + C::col(wn, j) + c16;
           if (n >= a.out_cols) continue;
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
@@ -575,26 +587,6 @@ __global__ void __launch_bounds__(256) k_gemm_splitk_reduce(GemmArgs a) {
   }
 }
 
-// Packs 4 consecutive-site values of one element into one LDS store.
-template <typename T>
-struct Quad;
-template <>
-struct Quad<__bf16> {
-  typedef uint64_t W;
-  __device__ static inline W pack(__bf16 a, __bf16 b, __bf16 c, __bf16 d) {
-    return (uint64_t)__builtin_bit_cast(uint16_t, a) | ((uint64_t)__builtin_bit_cast(uint16_t, b) << 16) |
-           ((uint64_t)__builtin_bit_cast(uint16_t, c) << 32) | ((uint64_t)__builtin_bit_cast(uint16_t, d) << 48);
-  }
-};
-template <>
-struct Quad<float> {
-  typedef u32x4 W;
-  __device__ static inline W pack(float a, float b, float c, float d) {
-    return u32x4{__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), __builtin_bit_cast(uint32_t, c),
-                 __builtin_bit_cast(uint32_t, d)};
-  }
-};
-
 // Site chunks actually used: slabs of BK sites per chunk as planned, at most
 // the planned (capacity) chunk count, from the device-side row count.
 __device__ inline int wgrad_chunks_dev(const WGradArgs& a, int rows, int BK) {
@@ -620,7 +612,7 @@ __device__ inline void store_wgrad_tile(const WGradArgs& a, const f32x4 (&acc)[C
     for (int i = 0; i < C::TM; ++i)
 #pragma unroll
       for (int j = 0; j < C::TN; ++j) {
-        const int bm = m0 / 16 + wm * C::TM + i, bn = n0 / 16 + wn * C::TN + j;
+        const int bm = (m0 + C::row(wm, i)) / 16, bn = (n0 + C::col(wn, j)) / 16;
         if (bm < MB && bn < NB) *(f32x4*)(part + ((int64_t)(bm * NB + bn) * 64 + lane) * 4) = acc[i][j];
       }
     return;
@@ -630,7 +622,7 @@ __device__ inline void store_wgrad_tile(const WGradArgs& a, const f32x4 (&acc)[C
   const float rcp_cseg = 1.f / (float)a.cseg;
 #pragma unroll
   for (int i = 0; i < C::TM; ++i) {
-    const int mb = m0 + wm * C::TM * 16 + i * 16 + g * 4;
+    const int mb = m0 + C::row(wm, i) + g * 4;
     const int f = div_small(mb, a.cseg, rcp_cseg), c = mb - f * a.cseg;
     int idx[4];
     bool wr[4], br[4];
@@ -642,7 +634,7 @@ __device__ inline void store_wgrad_tile(const WGradArgs& a, const f32x4 (&acc)[C
     }
 #pragma unroll
     for (int j = 0; j < C::TN; ++j) {
-      const int nn = n0 + wn * C::TN * 16 + j * 16 + c16;
+      const int nn = n0 + C::col(wn, j) + c16;
       if (nn >= a.c_out) continue;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
@@ -652,132 +644,6 @@ __device__ inline void store_wgrad_tile(const WGradArgs& a, const f32x4 (&acc)[C
           a.db[nn] = acc[i][j][r];
       }
     }
-  }
-}
-
-// Weight-gradient GEMM, split over sites (the K dimension).  A^T and delta^T
-// slabs are staged in LDS as [row of dW / col of dW][site]: each thread loads
-// 16-byte vectors (VE consecutive channels) of 4 consecutive sites and stores
-// them transposed, 4 sites per LDS write.  Loads of the next slab are issued
-// before the current slab's MFMAs.
-//
-// One launch serves a group of layers: workgroup tile t belongs to the layer l
-// with tile_beg[l] <= t < tile_beg[l + 1].
-template <typename T, class C>
-__global__ void __launch_bounds__(C::NT) k_wgrad(WGradGroup grp, ExtraTask x) {
-  constexpr int VE = C::VE, BK = C::BK, LDK = C::LDK, BM = C::BM, BN = C::BN, NT = C::NT;
-  constexpr int MV = BM / VE, NV = BN / VE;  // vectors across a slab row
-  static_assert(MV * (BK / 4) == NT && NV * (BK / 4) <= NT, "one quad of sites per thread");
-  typedef typename Quad<T>::W QW;
-  __shared__ __attribute__((aligned(16))) T As[BM * LDK];  // [m][site]
-  __shared__ __attribute__((aligned(16))) T Bs[BN * LDK];  // [n][site]
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / C::WN, wn = wave % C::WN;
-  const T one = Elem<T>::from_f32(1.f), zero = Elem<T>::from_f32(0.f);
-  // this thread's quad: sites 4*q .. 4*q+3 of a slab, vector mv / nv.  The quad
-  // index runs fastest so that a wavefront's transposed LDS writes spread over
-  // all banks (vector-fastest puts every vector of a quad on the same bank).
-  constexpr int NQ = BK / 4;
-  const int qa = tid % NQ, mv = tid / NQ;
-  const int qb = tid % NQ, nvv = tid / NQ;
-  const bool b_active = tid < NV * NQ;
-  if (run_extra<T>(x)) return;
-
-  for (int t = blockIdx.x; t < grp.tile_beg[grp.n]; t += own_grid(x)) {
-    int l = 0;
-    while (l + 1 < grp.n && t >= grp.tile_beg[l + 1]) ++l;
-    const WGradArgs& a = grp.L[l];
-    const int tile = t - grp.tile_beg[l];
-    const int rows = a.rows_dev ? (*a.rows_dev + a.rows_add) : a.rows_host;
-    const int tiles_m = a.Mpad / BM, tiles_n = a.Npad / BN;
-    const int nch = wgrad_chunks_dev(a, rows, BK);
-    const int per = ((rows + nch - 1) / nch + BK - 1) / BK * BK;
-    const int m_gather = a.A * a.cseg;
-    const int m_rows = a.m_ones >= 0 ? a.m_ones + 1 : m_gather;  // rows of dW / db that are read back
-    const T* src = (const T*)a.src;
-    const T* dsrc = (const T*)a.dsrc;
-    const int tn = tile % tiles_n;
-    const int tq = tile / tiles_n;
-    const int tm = tq % tiles_m;
-    const int chunk = tq / tiles_m;
-    if (chunk >= nch) continue;  // fewer rows than the plan allowed for
-    const int m0 = tm * BM, n0 = tn * BN;
-    const int o_beg = chunk * per;
-    const int o_end = min(rows, o_beg + per);
-    f32x4 acc[C::TM][C::TN];
-#pragma unroll
-    for (int i = 0; i < C::TM; ++i)
-#pragma unroll
-      for (int j = 0; j < C::TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    u32x4 ra[4], rb[4];
-    const int m = m0 + mv * VE;
-    const int f_of_m = m < m_gather ? m / a.cseg : 0;
-    const int c_of_m = m < m_gather ? m - f_of_m * a.cseg : 0;
-    const int n = n0 + nvv * VE;
-    // source rows of this thread's 4 sites, fetched one slab ahead of their use
-    int rnext[4];
-    auto load_rows = [&](int ob) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int o = ob + 4 * qa + i;
-        int r = -1;
-        if (o < o_end && m < m_gather) r = a.rmap ? a.rmap[(int64_t)o * a.A + f_of_m] : o;
-        rnext[i] = r;
-      }
-    };
-    auto load = [&](int ob) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int o = ob + 4 * qa + i;
-        u32x4 val = {0u, 0u, 0u, 0u};
-        if (o < o_end) {
-          if (m < m_gather) {
-            val = *(const u32x4*)(src + (int64_t)rnext[i] * a.src_stride + c_of_m);
-          } else {
-            T* vv = (T*)&val;
-#pragma unroll
-            for (int j = 0; j < VE; ++j) vv[j] = (m + j == a.m_ones) ? one : zero;
-          }
-        }
-        ra[i] = val;
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int o = ob + 4 * qb + i;
-        u32x4 val = {0u, 0u, 0u, 0u};
-        if (b_active && o < o_end && n < a.dsrc_cols) val = *(const u32x4*)(dsrc + (int64_t)o * a.dsrc_stride + n);
-        rb[i] = val;
-      }
-    };
-    load_rows(o_beg);
-    if (o_beg < o_end) {
-      load(o_beg);
-      load_rows(o_beg + BK);
-    }
-    for (int ob = o_beg; ob < o_end; ob += BK) {
-#pragma unroll
-      for (int j = 0; j < VE; ++j)
-        *(QW*)(As + (mv * VE + j) * LDK + 4 * qa) =
-            Quad<T>::pack(((const T*)&ra[0])[j], ((const T*)&ra[1])[j], ((const T*)&ra[2])[j], ((const T*)&ra[3])[j]);
-      if (b_active) {
-#pragma unroll
-        for (int j = 0; j < VE; ++j)
-          *(QW*)(Bs + (nvv * VE + j) * LDK + 4 * qb) = Quad<T>::pack(((const T*)&rb[0])[j], ((const T*)&rb[1])[j],
-                                                                      ((const T*)&rb[2])[j], ((const T*)&rb[3])[j]);
-      }
-      __syncthreads();
-      if (ob + BK < o_end) {
-        load(ob + BK);
-        load_rows(ob + 2 * BK);
-      }
-      mma_slab<T, C>(As, Bs, acc, wm, wn, lane);
-      __syncthreads();
-    }
-
-    store_wgrad_tile<C>(a, acc, chunk, nch, m0, n0, wm, wn, lane, m_rows, m_gather);
   }
 }
 
@@ -827,12 +693,12 @@ __device__ inline void mma_slab_tr(const __bf16* As, const __bf16* Bs, f32x4 (&a
     const int ha = site_row_swz<BM * 2>(row), hb = site_row_swz<BN * 2>(row);
     bf16x8 bv[C::TN];
 #pragma unroll
-    for (int j = 0; j < C::TN; ++j) bv[j] = tr_operand<BN>(Bs + row * BN + (((wn * C::TN + j) ^ hb) << 4) + e4);
+    for (int j = 0; j < C::TN; ++j) bv[j] = tr_operand<BN>(Bs + row * BN + (((C::col(wn, j) / 16) ^ hb) << 4) + e4);
 #pragma unroll
     for (int i = 0; i < C::TM; ++i) {
-      bf16x8 av = tr_operand<BM>(As + row * BM + (((wm * C::TM + i) ^ ha) << 4) + e4);
+      bf16x8 av = tr_operand<BM>(As + row * BM + (((C::row(wm, i) / 16) ^ ha) << 4) + e4);
       if constexpr (ONES) {
-        if (wm * C::TM * 16 + i * 16 + q == m_loc) {
+        if (C::row(wm, i) + q == m_loc) {
 #pragma unroll
           for (int e = 0; e < 8; ++e) av[e] = (__bf16)(kb + 8 * g + e < valid ? 1.f : 0.f);
         }
@@ -840,6 +706,36 @@ __device__ inline void mma_slab_tr(const __bf16* As, const __bf16* Bs, f32x4 (&a
 #pragma unroll
       for (int j = 0; j < C::TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv[j], acc[i][j], 0, 0, 0);
     }
+  }
+}
+
+// The same for float32, whose 16x16x4 MFMA takes one site per lane group: lane
+// (g, q) reads column q of a 16-column block at site kb + g, straight from the
+// slab as stored.  Blocks are swizzled by the site (block b of site r at block
+// slot b ^ (r % 4)), so the four sites of a read lie in different banks.  Only
+// the wave's first LM row blocks and LN column blocks are computed.
+template <class C, int BKS, bool ONES, int LM, int LN>
+__device__ inline void mma_slab_sites(const float* As, const float* Bs, f32x4 (&acc)[C::TM][C::TN], int wm, int wn,
+                                      int lane, int m_loc, int valid) {
+  constexpr int BM = C::BM, BN = C::BN;
+  const int g = lane >> 4, q = lane & 15;
+#pragma unroll
+  for (int kb = 0; kb < BKS; kb += 4) {
+    const int site = kb + g;
+    float av[LM], bv[LN];
+#pragma unroll
+    for (int i = 0; i < LM; ++i) {
+      av[i] = As[site * BM + (((C::row(wm, i) / 16) ^ g) << 4) + q];
+      if constexpr (ONES)
+        if (C::row(wm, i) + q == m_loc) av[i] = site < valid ? 1.f : 0.f;
+    }
+#pragma unroll
+    for (int j = 0; j < LN; ++j) bv[j] = Bs[site * BN + (((C::col(wn, j) / 16) ^ g) << 4) + q];
+#pragma unroll
+    for (int i = 0; i < LM; ++i)
+#pragma unroll
+      for (int j = 0; j < LN; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i], bv[j], acc[i][j], 0, 0, 0);
   }
 }
 
@@ -854,24 +750,27 @@ __device__ inline void wait_vmcnt_steps(int steps) {
   }
 }
 
-// Weight gradients, bf16: the tiles and site chunks of k_wgrad, but the operand
-// slabs (BKS sites) go from memory straight into LDS as stored, one site per
-// LDS row (buffer loads with an LDS destination; an offset past the buffer
-// reads zero), and the MFMA operands are read across sites with the LDS
-// transpose read.  NST stages: the loads of NST - 1 slabs fly while one is
+// Weight-gradient GEMM, split over sites (the K dimension).  One launch serves a
+// group of layers: workgroup tile t belongs to the layer l with tile_beg[l] <= t
+// < tile_beg[l + 1].  The operand slabs (BKS sites) go from memory straight into
+// LDS as stored, one site per LDS row (bf16: buffer loads with an LDS
+// destination, an offset past the buffer reads zero; float32: loads from 64-bit
+// addresses), and the MFMA operands are read across sites (bf16: with the LDS
+// transpose read).  NST stages: the loads of NST - 1 slabs fly while one is
 // multiplied, one barrier per slab.  The window rows of a slab reach LDS the
 // same way, into a ring of NST slots, issued with the operand loads NST - 1
 // slabs before the ones that read them (so that waiting for a slab's operands
 // also covers the window rows of the slab NST - 1 after it).  Every wave issues
 // the same number of window-row loads per slab (unused ones read zero into a
 // spare row), which keeps the wait counts compile-time constants.
-template <class C, int BKS, int NST>
-__global__ void __launch_bounds__(C::NT) k_wgrad_tr(WGradGroup grp, ExtraTask x) {
-  using T = __bf16;
+template <typename T, class C, int BKS, int NST>
+__global__ void __launch_bounds__(C::NT) k_wgrad(WGradGroup grp, ExtraTask x) {
+  constexpr bool B16 = sizeof(T) == 2;
+  constexpr int VE = C::VE;
   constexpr int BM = C::BM, BN = C::BN, NT = C::NT, BK = C::BK;
-  static_assert(NT == 256 && BM == 128 && BK % BKS == 0 && BKS % C::KB == 0 && NST >= 2 && NST <= 4,
+  static_assert(NT == 256 && BM == 128 && BK % BKS == 0 && BKS % (B16 ? C::KB : 4) == 0 && NST >= 2 && NST <= 4,
                 "slab and thread layout below");
-  constexpr int ACH = BM / 8, BCH = BN / 8;  // 16-byte chunks per LDS row
+  constexpr int ACH = BM / VE, BCH = BN / VE;  // 16-byte chunks per LDS row
   constexpr int AV = BKS * ACH / NT, BV = BKS * BCH / NT;
   static_assert(AV * NT == BKS * ACH && BV * NT == BKS * BCH, "slab splits evenly over the threads");
   constexpr int LPS = AV + BV;                       // operand loads per thread and slab
@@ -894,8 +793,15 @@ __global__ void __launch_bounds__(C::NT) k_wgrad_tr(WGradGroup grp, ExtraTask x)
   // (the row bits the swizzle reads do not change with j), and the logical
   // column chunk each slot holds
   const int ra0 = tid / ACH, ta = tid % ACH, rb0 = tid / BCH, tb = tid % BCH;
-  const int ca = 2 * ((ta >> 1) ^ site_row_swz<BM * 2>(ra0)) + (ta & 1);
-  const int cb = 2 * ((tb >> 1) ^ site_row_swz<BN * 2>(rb0)) + (tb & 1);
+  static_assert(NT / ACH % (B16 ? 16 : 4) == 0 && NT / BCH % (B16 ? 16 : 4) == 0, "the row bits the swizzle reads");
+  int ca, cb;
+  if constexpr (B16) {
+    ca = 2 * ((ta >> 1) ^ site_row_swz<BM * 2>(ra0)) + (ta & 1);
+    cb = 2 * ((tb >> 1) ^ site_row_swz<BN * 2>(rb0)) + (tb & 1);
+  } else {
+    ca = 4 * ((ta >> 2) ^ (ra0 & 3)) + (ta & 3);
+    cb = 4 * ((tb >> 2) ^ (rb0 & 3)) + (tb & 3);
+  }
 
   for (int t = blockIdx.x; t < grp.tile_beg[grp.n]; t += own_grid(x)) {
     int l = 0;
@@ -924,11 +830,11 @@ __global__ void __launch_bounds__(C::NT) k_wgrad_tr(WGradGroup grp, ExtraTask x)
       for (int j = 0; j < C::TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     const int A = a.A;
-    const int ma = m0 + 8 * ca;  // first column of this thread's A chunk: window position fa, channel cola
+    const int ma = m0 + VE * ca;  // first column of this thread's A chunk: window position fa, channel cola
     const bool a_col = ma < m_gather;
     const int fa = a_col ? ma / a.cseg : 0;
     const int cola = ma - fa * a.cseg;
-    const int nb = n0 + 8 * cb;
+    const int nb = n0 + VE * cb;
     const bool b_col = nb < a.dsrc_cols;
     const bool has_r = a.rmap != nullptr;
     const int r_loads = has_r ? (BKS * A + 63) / 64 : 0;  // 64-dword loads that carry window rows
@@ -938,6 +844,16 @@ __global__ void __launch_bounds__(C::NT) k_wgrad_tr(WGradGroup grp, ExtraTask x)
     const u32x4 rsA = buffer_rsrc(a.src, GATHER_SRC_BYTES);
     const u32x4 rsB = buffer_rsrc(a.dsrc, GATHER_SRC_BYTES);
     const u32x4 rsR = buffer_rsrc(a.rmap, GATHER_SRC_BYTES);
+    const T* src = (const T*)a.src;
+    const T* dsrc = (const T*)a.dsrc;
+    const uint32_t src_bytes = (uint32_t)src_stride * (uint32_t)sizeof(T), dsrc_bytes = (uint32_t)dsrc_stride * (uint32_t)sizeof(T);
+    const int32_t* rmap = a.rmap;
+    const void* zero = a.zero;
+    // this wave's blocks that hold part of the result
+    const int live_m = __builtin_amdgcn_readfirstlane(
+        (min(m_rows - m0, BM) - wm * 16 + 16 * C::WM - 1) / (16 * C::WM));
+    const int live_n = __builtin_amdgcn_readfirstlane(
+        (min(a.c_out - n0, BN) - wn * 16 + 16 * C::WN - 1) / (16 * C::WN));
     const float rcpA = 1.f / (float)A;
     // window rows of slab s (sites ob .. ob + BKS - 1, A entries each,
     // contiguous) into ring slot s % NST: wave w's i-th load takes dwords
@@ -951,34 +867,49 @@ __global__ void __launch_bounds__(C::NT) k_wgrad_tr(WGradGroup grp, ExtraTask x)
         const bool used = s < nsl && k < r_loads;
         const int d = 64 * k + lane;
         const bool live = used && d < BKS * A && ob + div_small(d, A, rcpA) < o_end;
-        dma4(rsR, used ? dst + (uint32_t)k * 256u : lds_spare, live ? (uint32_t)(ob * A + d) * 4u : GATHER_SRC_BYTES);
+        const uint32_t to = used ? dst + (uint32_t)k * 256u : lds_spare;
+        if constexpr (B16)
+          dma4(rsR, to, live ? (uint32_t)(ob * A + d) * 4u : GATHER_SRC_BYTES);
+        else
+          dma4_at(to, (const void*)(live ? (uint64_t)(rmap + ((int64_t)ob * A + d)) : (uint64_t)zero));
       }
     };
     // operand slab s into stage s % NST, reading its window rows from ring slot s % NST
     auto issue_slab = [&](int s) {
       const int ob = o_beg + s * BKS;
-      const uint32_t sa = lds_s + (uint32_t)((s % NST) * STG) * 2u, sb = sa + BM * BKS * 2;
+      const uint32_t sa = lds_s + (uint32_t)((s % NST) * STG * (int)sizeof(T)), sb = sa + BM * BKS * (int)sizeof(T);
       const int32_t* R = Rr + (s % NST) * RSLOT;
-      uint32_t offa[AV];
+      int srow[AV];
 #pragma unroll
       for (int j = 0; j < AV; ++j) {  // every window row read before the first load goes out
         const int r = ra0 + j * (NT / ACH);
         const int o = ob + r;
-        const int srow = has_r ? R[r * A + fa] : o;
-        offa[j] = a_col && o < o_end ? (uint32_t)(srow * src_stride + cola) * 2u : GATHER_SRC_BYTES;
+        srow[j] = has_r ? R[r * A + fa] : o;
+        if (!a_col || o >= o_end) srow[j] = -1;
       }
 #pragma unroll
-      for (int j = 0; j < AV; ++j) dma16(rsA, sa + (uint32_t)(wave_u * 64 + j * NT) * 16u, offa[j]);
+      for (int j = 0; j < AV; ++j) {
+        const uint32_t to = sa + (uint32_t)(wave_u * 64 + j * NT) * 16u;
+        if constexpr (B16)
+          dma16(rsA, to, srow[j] >= 0 ? (uint32_t)(srow[j] * src_stride + cola) * 2u : GATHER_SRC_BYTES);
+        else
+          dma16_at(to, (const void*)(srow[j] >= 0 ? (uint64_t)(src + cola) + (uint64_t)(uint32_t)srow[j] * src_bytes
+                                                  : (uint64_t)zero));
+      }
 #pragma unroll
       for (int j = 0; j < BV; ++j) {
         const int o = ob + rb0 + j * (NT / BCH);
-        dma16(rsB, sb + (uint32_t)(wave_u * 64 + j * NT) * 16u,
-              b_col && o < o_end ? (uint32_t)(o * dsrc_stride + nb) * 2u : GATHER_SRC_BYTES);
+        const uint32_t to = sb + (uint32_t)(wave_u * 64 + j * NT) * 16u;
+        const bool on = b_col && o < o_end;
+        if constexpr (B16)
+          dma16(rsB, to, on ? (uint32_t)(o * dsrc_stride + nb) * 2u : GATHER_SRC_BYTES);
+        else
+          dma16_at(to, (const void*)(on ? (uint64_t)(dsrc + nb) + (uint64_t)(uint32_t)o * dsrc_bytes : (uint64_t)zero));
       }
     };
     // the bias row (softmax layer): the wave whose rows hold it patches its operand
     const int m_loc = a.m_ones - m0;
-    const bool ones = a.m_ones >= 0 && m_loc >= wm * C::TM * 16 && m_loc < (wm + 1) * C::TM * 16;
+    const bool ones = a.m_ones >= 0 && m_loc >= 0 && m_loc < BM && m_loc / 16 % C::WM == wm;
 
     if (nsl > 0) {
       // window rows of the first NST - 1 slabs, their operands, then (once
@@ -999,8 +930,9 @@ __global__ void __launch_bounds__(C::NT) k_wgrad_tr(WGradGroup grp, ExtraTask x)
     // the slab loop, with the bias-row patch compiled into a copy of its own
     // (a branch per slab made the compiler copy the accumulators between the
     // two MFMA sequences on every slab)
-    auto slab_loop = [&](auto ones_c) {
+    auto slab_loop = [&](auto ones_c, auto lm_c, auto ln_c) {
       constexpr bool ONES = decltype(ones_c)::value;
+      constexpr int LM = decltype(lm_c)::value, LN = decltype(ln_c)::value;
       for (int s = 0; s < nsl; ++s) {
         // slab s and the window rows of slab s + NST - 1 have landed (this
         // wave's, and after the barrier every wave's); every wave is done with
@@ -1024,13 +956,24 @@ __global__ void __launch_bounds__(C::NT) k_wgrad_tr(WGradGroup grp, ExtraTask x)
         if (s + NST - 1 < nsl) issue_slab(s + NST - 1);
         const T* As = smem + (s % NST) * STG;
         const int valid = o_end - (o_beg + s * BKS);
-        mma_slab_tr<C, BKS, ONES>(As, As + BM * BKS, acc, wm, wn, lane, m_loc, valid);
+        if constexpr (B16)
+          mma_slab_tr<C, BKS, ONES>(As, As + BM * BKS, acc, wm, wn, lane, m_loc, valid);
+        else
+          mma_slab_sites<C, BKS, ONES, LM, LN>(As, As + BM * BKS, acc, wm, wn, lane, m_loc, valid);
       }
     };
+    // (float32 also by the live blocks of this wave, as in the gather GEMM; every
+    // wave passes the same barriers in whichever copy it runs)
+    constexpr std::integral_constant<int, C::TM> all_m{};
+    constexpr std::integral_constant<int, C::TN> all_n{};
     if (ones)
-      slab_loop(std::integral_constant<bool, true>{});
+      slab_loop(std::integral_constant<bool, true>{}, all_m, all_n);
+    else if constexpr (B16)
+      slab_loop(std::integral_constant<bool, false>{}, all_m, all_n);
     else
-      slab_loop(std::integral_constant<bool, false>{});
+      with_count<C::TM == 4 ? 2 : 1, C::TM>(live_m, [&](auto lm_c) {
+        with_count<2, C::TN>(live_n, [&](auto ln_c) { slab_loop(std::integral_constant<bool, false>{}, lm_c, ln_c); });
+      });
 
     store_wgrad_tile<C>(a, acc, chunk, nch, m0, n0, wm, wn, lane, m_rows, m_gather);
   }
@@ -1138,18 +1081,18 @@ hipError_t launch_gemm(bool bf16, const GemmArgs& args, int64_t max_rows, hipStr
   if (args.A < 1 || args.A > AMAX) return hipErrorInvalidValue;  // window tables hold at most AMAX entries a row
   GemmArgs a = args;
   a.rows_cap = (int32_t)max_rows;
-  if (a.pool_fwd && (a.route || a.ksplit != 1 || !gemm_routes(bf16, a.cfg) || a.row_begin != 0 || !a.pslot ||
+  if (a.pool_fwd && (a.route || a.ksplit != 1 || a.row_begin != 0 || !a.pslot ||
                      !a.pool_out || !a.pool_argmax || !a.rows_dev ||
                      (a.epi != EPI_BIAS_RELU && a.epi != EPI_BIAS_LRELU)))
     return hipErrorInvalidValue;
   if (a.route) {  // pooling backward in the epilogue: one partial per row tile
     const int bm = gemm_bm(bf16, a.cfg);
-    if (a.epi != EPI_STORE || a.ksplit != 1 || !gemm_routes(bf16, a.cfg) || (a.route_ac != 0 && a.route_ac != 4) ||
+    if (a.epi != EPI_STORE || a.ksplit != 1 || (a.route_ac != 0 && a.route_ac != 4) ||
         !a.pr.part || !a.pr.Rp || !a.pr.argmax || !a.pr.dZ || !a.pr.X_pool || (a.route_ac == 4 && !a.pr.gmask) ||
         a.pr.cp != a.out_cols || a.pr.stride != a.pr.cp || (max_rows - a.row_begin + bm - 1) / bm > a.pr.PM)
       return hipErrorInvalidValue;
   }
-  if (a.cfg == GEMM_DIRECT) return bf16 ? launch_gemm_direct(a, max_rows, st) : hipErrorInvalidValue;
+  if (a.cfg == GEMM_DIRECT) return launch_gemm_direct(bf16, a, max_rows, st);
   if (bf16)
     launch_gemm_t<__bf16>(a, max_rows, st);
   else
@@ -1158,7 +1101,7 @@ hipError_t launch_gemm(bool bf16, const GemmArgs& args, int64_t max_rows, hipStr
 }
 
 GemmPlan plan_gemm(bool bf16, int64_t max_rows, int N, int K, bool short_rows, int direct_max) {
-  // bf16 launches with few output tiles (at the row bound) go to the
+  // Launches with few output tiles (at the row bound) go to the
   // direct-operand kernel, whose waves split K and so keep many loads in flight
   // per tile; launches with more tiles keep the LDS-tiled kernel, whose slabs
   // stream through LDS stages shared by the tile's waves.  (Measured on the
@@ -1168,17 +1111,23 @@ GemmPlan plan_gemm(bool bf16, int64_t max_rows, int N, int K, bool short_rows, i
   // at 3.3k; forward with the pooling forward even at 204 tiles; the softmax
   // layer's forward, 236 tiles, 7.2 us direct against 6.6 LDS-tiled.  The
   // callers pass 600, 256 and 128.)
+  // float32 (one lane holds 4 k, not 8: twice the loads per k block and sixteen
+  // times the MFMA time) goes there for up to 128 tiles and K <= 512, where it
+  // saves the split-K reduce and lets the pooling passes ride in the epilogue:
+  // DeepCNet(4,20) at batch 8, K = 80 .. 320: forwards 6.2 + 3.5 (reduce) + 2.5
+  // (pooling) -> 7.5 us, input gradients 7.0 + 3.7 + 4.8 -> 13.7 us; but K = 1000
+  // at 20 tiles 20.1 us against 6.7 + 5.0.
   const int64_t direct_tiles = ((max_rows + DIRECT_BM - 1) / DIRECT_BM) * ((N + DIRECT_BN - 1) / DIRECT_BN);
-  if (bf16 && direct_tiles <= direct_max && K <= 2048) {
-    // waves per tile so that each sums at most about four 32-wide k blocks,
-    // and more while the grid stays small
+  if (direct_tiles <= (bf16 ? direct_max : 128) && K <= (bf16 ? 2048 : 512)) {
+    // waves per tile so that each sums at most about four k blocks (32 wide, 16
+    // for float32), and more while the grid stays small
     GemmPlan p;
     p.cfg = GEMM_DIRECT;
     p.BN = DIRECT_BN;
     p.Npad = (int)round_up(N, DIRECT_BN);
     p.Kpad = (int)round_up(K, 64);
     p.ksplit = 1;
-    const int ksteps = (K + 31) / 32;
+    const int ksteps = bf16 ? (K + 31) / 32 : (K + 15) / 16;
     const int64_t tiles = ((max_rows + DIRECT_BM - 1) / DIRECT_BM) * (p.Npad / DIRECT_BN);
     int sk = 1;
     while (sk < 4 && sk * 4 < ksteps) sk *= 2;
@@ -1197,7 +1146,21 @@ GemmPlan plan_gemm(bool bf16, int64_t max_rows, int N, int K, bool short_rows, i
   const int64_t n128 = (N + 127) / 128 * 128, n64 = (N + 63) / 64 * 64;
   auto tiles = [&](int bm, int64_t npad, int bn) { return ((max_rows + bm - 1) / bm) * (npad / bn); };
   GemmPlan p;
-  if (!short_rows && n128 <= n64 && tiles(128, n128, 128) >= 256)
+  // float32, whose MFMAs take sixteen times as long: smaller tiles while a launch
+  // has few of them (a compute unit with one tile more than the others holds the
+  // launch up for its whole time: DeepCNet(5,50)'s fourth forward 50.4 us in 264
+  // 128 x 64 tiles, 41.6 in 528 of 64 x 64; its third input gradient 31.7 us in
+  // 770 64 x 64 tiles at the row bound, 28.5 in 32 x 64), and 128 rows only where K
+  // is long enough to make up for a taller tile's setup and epilogue (40 channels
+  // wide, K = 120: 14.3 us against 12.4 with 64 rows; 150 wide, K = 400: 40.0
+  // against 45.1).
+  if (!bf16) {
+    const bool tall = !short_rows && K > 4 * BK;
+    p.cfg = tall && n128 <= n64 && tiles(128, n128, 128) >= 256 ? 0
+            : tall && tiles(128, n64, 64) >= 512                ? 1
+            : tiles(64, n64, 64) >= 1024                        ? 2
+                                                                : 3;
+  } else if (!short_rows && n128 <= n64 && tiles(128, n128, 128) >= 256)
     p.cfg = 0;
   else if (!short_rows && tiles(128, n64, 64) >= 256)
     p.cfg = 1;
@@ -1216,14 +1179,6 @@ GemmPlan plan_gemm(bool bf16, int64_t max_rows, int N, int K, bool short_rows, i
   return p;
 }
 
-// sites per slab and LDS stages of the bf16 weight-gradient tiles
-#ifndef WG_SLAB_128
-#define WG_SLAB_128 32
-#define WG_STAGES_128 4
-#define WG_SLAB_64 32
-#define WG_STAGES_64 3
-#endif
-
 hipError_t launch_wgrad(bool bf16, int cfg, const WGradArgs* layers, int n, hipStream_t st, const ExtraTask* extra) {
   // cfg: 0 = 128 x 128 tiles, 1 = 128 x 64
   if (n < 1 || n > MAX_WG_LAYERS) return hipErrorInvalidValue;
@@ -1239,16 +1194,18 @@ hipError_t launch_wgrad(bool bf16, int cfg, const WGradArgs* layers, int n, hipS
     g.tile_beg[l + 1] = g.tile_beg[l] + (layers[l].Mpad / 128) * (layers[l].Npad / BN) * layers[l].nchunks;
   }
   const int grid = std::min(std::max(g.tile_beg[n], 1), device_grid_limit()) + (x.kind ? x.blocks : 0);
+  // sites per slab and LDS stages: as many stages as leave two (128 x 128) or
+  // three (128 x 64) workgroups per compute unit
   if (bf16) {
     if (cfg == 0)
-      hipLaunchKernelGGL((k_wgrad_tr<C128x128<__bf16>, WG_SLAB_128, WG_STAGES_128>), dim3(grid), dim3(256), 0, st, g, x);
+      hipLaunchKernelGGL((k_wgrad<__bf16, C128x128<__bf16>, 32, 4>), dim3(grid), dim3(256), 0, st, g, x);
     else
-      hipLaunchKernelGGL((k_wgrad_tr<C128x64<__bf16>, WG_SLAB_64, WG_STAGES_64>), dim3(grid), dim3(256), 0, st, g, x);
+      hipLaunchKernelGGL((k_wgrad<__bf16, C128x64<__bf16>, 32, 3>), dim3(grid), dim3(256), 0, st, g, x);
   } else {
     if (cfg == 0)
-      hipLaunchKernelGGL((k_wgrad<float, C128x128<float>>), dim3(grid), dim3(256), 0, st, g, x);
+      hipLaunchKernelGGL((k_wgrad<float, GCfg<float, 2, 2, 4, 4>, 16, 4>), dim3(grid), dim3(256), 0, st, g, x);
     else
-      hipLaunchKernelGGL((k_wgrad<float, C128x64<float>>), dim3(grid), dim3(256), 0, st, g, x);
+      hipLaunchKernelGGL((k_wgrad<float, C128x64<float>, 16, 4>), dim3(grid), dim3(256), 0, st, g, x);
   }
   return hipGetLastError();
 }

@@ -103,6 +103,7 @@ struct ExtraTask {
 
 struct GemmArgs {
   const void* src;
+  const void* zero;  // float32: 16 zero bytes, read for rows without a window entry and past K
   int32_t src_stride;
   const int32_t* rmap;
   int32_t A;
@@ -177,9 +178,6 @@ constexpr int MASK_MODE = -3;
 // entry use that), so every source row must end below it.
 constexpr uint32_t GATHER_SRC_BYTES = 0x7ffffff0u;
 
-// Whether a tile shape stages its output tile through LDS (16-byte stores), as
-// the pooling backward in the epilogue needs.
-bool gemm_routes(bool bf16, int cfg);
 // Row tile height of a tile shape.
 int gemm_bm(bool bf16, int cfg);
 
@@ -193,7 +191,7 @@ struct GemmPlan {
   int sk = 1;  // direct kernel (cfg = GEMM_DIRECT): waves per workgroup splitting K
 };
 
-// cfg value of the bf16 direct-operand kernel (gemm_direct.hip): 32 x 64 output
+// cfg value of the direct-operand kernel (gemm_direct.hip): 32 x 64 output
 // tiles, each wave loading its MFMA operands straight from memory
 constexpr int GEMM_DIRECT = 4;
 constexpr int DIRECT_BM = 32, DIRECT_BN = 64;
@@ -204,6 +202,7 @@ constexpr int DIRECT_BM = 32, DIRECT_BN = 64;
 //   A(o, m_ones) = 1 when m_ones >= 0 (row m_ones of the result is then db)
 struct WGradArgs {
   const void* src;
+  const void* zero;  // float32: 16 zero bytes, read past a chunk's sites and the operands' columns
   int32_t src_stride;
   const int32_t* rmap;
   int32_t A;
@@ -248,7 +247,7 @@ constexpr int WG_BM = 128;
 inline int wgrad_bn(int c_out) { return (c_out + 127) / 128 * 128 <= (c_out + 63) / 64 * 64 ? 128 : 64; }
 
 hipError_t launch_gemm(bool bf16, const GemmArgs& a, int64_t max_rows, hipStream_t st);
-hipError_t launch_gemm_direct(const GemmArgs& a, int64_t max_rows, hipStream_t st);
+hipError_t launch_gemm_direct(bool bf16, const GemmArgs& a, int64_t max_rows, hipStream_t st);
 // Convolution forward on the vector ALUs for layers with few input channels:
 // at most NARROW_KMAX products per output (A * cin, 1 <= cin <= 4, within one
 // 16-byte vector of input channels), a window list, the bias-rectifier epilogue,
