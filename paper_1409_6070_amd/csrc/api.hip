@@ -569,7 +569,7 @@ static sscn_status rulebook_build(sscn_net* net, const int32_t* d_coords, const 
   a.coords = d_coords;
   a.n = n;
   a.sample_begin = batch > 0 ? d_sample_begin : nullptr;
-  // window-list segments: LISTS_WPB bitmap words of a layer per workgroup (one
+  // window-list segments: lw.words bitmap words of a layer per workgroup (one
   // workgroup for an empty batch, which writes the ground rows), 256 caller
   // sites or samples per workgroup
   ListsWork lw;
@@ -580,8 +580,11 @@ static sscn_status rulebook_build(sscn_net* net, const int32_t* d_coords, const 
     lw.blk[lw.nseg + 1] = lw.blk[lw.nseg] + (int)std::max<int64_t>(1, blocks);
     ++lw.nseg;
   };
+  int64_t words = 0;
+  for (int s = 0; s < net->nlayers; ++s) words += (int64_t)batch * net->L[s].S * net->L[s].Wd;
+  lw.words = lists_words(words);
   for (int s = 0; s < net->nlayers; ++s)
-    add_seg(0, s, ((int64_t)batch * net->L[s].S * net->L[s].Wd + LISTS_WPB - 1) / LISTS_WPB);
+    add_seg(0, s, ((int64_t)batch * net->L[s].S * net->L[s].Wd + lw.words - 1) / lw.words);
   add_seg(2, 0, ((int64_t)n + 255) / 256);
   add_seg(3, 0, ((int64_t)batch + 255) / 256);
   if (timed(net, SSCN_KC_RULEBOOK, st, [&] { return launch_rulebook(a, lw, net->max_words, st); }) != hipSuccess)

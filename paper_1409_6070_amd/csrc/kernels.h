@@ -7,15 +7,22 @@
 
 namespace sscn {
 
-// Bitmap words of a layer per workgroup of the window-list kernel.
-constexpr int LISTS_WPB = 32;
+// Bitmap words of a layer per workgroup of the window-list kernel, for a build of
+// `words` bitmap words in all: 32 (eight threads a word) while that makes at
+// most a round of workgroups (2048 on 256 compute units), else up to 256.
+inline int lists_words(int64_t words) {
+  int w = 32;
+  while (w < 256 && words > (int64_t)w * 2048) w *= 2;
+  return w;
+}
 
 // Segments of the window-list kernel: kind 0 = the rows of layer `layer`
 // (their keys, R of that layer, the transposes of the layer above), with
-// ceil(batch * S * Wd / LISTS_WPB) workgroups; 2 = caller-site rows and 3 = head
+// ceil(batch * S * Wd / words) workgroups; 2 = caller-site rows and 3 = head
 // rows, 256 per workgroup; segment i owns workgroups [blk[i], blk[i+1]).
 struct ListsWork {
   int32_t nseg;
+  int32_t words;  // lists_words
   int32_t kind[MAX_LAYERS + 2];
   int32_t layer[MAX_LAYERS + 2];
   int32_t blk[MAX_LAYERS + 3];

@@ -34,6 +34,8 @@
 #include "common.h"
 #include "kernels.h"
 
+#include <type_traits>
+
 namespace sscn {
 
 // Clears both input bitmaps and the error and counter words (when a workspace
@@ -156,13 +158,47 @@ __device__ inline int insert_sample(const int32_t* coords, int beg, int end, int
   return err;
 }
 
+// Bits 0, 2, 4, .. of v, packed into 32 bits.
+__device__ inline uint64_t even_bits(uint64_t v) {
+  v &= 0x5555555555555555ull;
+  v = (v | (v >> 1)) & 0x3333333333333333ull;
+  v = (v | (v >> 2)) & 0x0f0f0f0f0f0f0f0full;
+  v = (v | (v >> 4)) & 0x00ff00ff00ff00ffull;
+  v = (v | (v >> 8)) & 0x0000ffff0000ffffull;
+  return (v | (v >> 16)) & 0xffffffffull;
+}
+
+// One output row from the OR of its input rows, in place: row (nw words, the
+// bits past the grid zero) becomes bit X = any of bits [a X, a X + r), a a power
+// of two.  The dilation doubles its reach (log2 r shifts of the whole row), then
+// every a-th bit is kept (log2 a rounds of packing the even bits): a few dozen
+// operations a word where testing each output bit's range took its whole row
+// of tests (layers of a 192 x 192 grid, three words a row: 26.4 -> 12.9 us for
+// the launch at batch 64).
+__device__ inline void dilate_row(uint64_t* row, int nw, int a, int r) {
+  for (int len = 1; len < r;) {
+    const int sh = min(len, r - len), ws = sh >> 6, bs = sh & 63;
+    for (int w = 0; w < nw; ++w) {  // words >= w only: in place
+      const uint64_t lo = w + ws < nw ? row[w + ws] : 0ull, hi = w + ws + 1 < nw ? row[w + ws + 1] : 0ull;
+      row[w] |= bs ? (lo >> bs) | (hi << (64 - bs)) : lo;
+    }
+    len += sh;
+  }
+  for (int st = a; st > 1; st >>= 1) {
+    for (int w = 0; w < (nw + 1) / 2; ++w) {
+      const uint64_t lo = row[2 * w], hi = 2 * w + 1 < nw ? row[2 * w + 1] : 0ull;
+      row[w] = even_bits(lo) | (even_bits(hi) << 32);
+    }
+    nw = (nw + 1) / 2;
+  }
+}
+
 // Layer s of sample b, b = blockIdx / nlayers, s = blockIdx % nlayers (one
 // wave): the sample's input bitmap goes to LDS (read from the inserted bitmap,
 // or, with the sites grouped by sample, built here from the sample's own
 // sites by LDS atomic ORs, the input layer's wave storing it); each lane takes whole output
-// rows, ORs the input rows of their squares into its own row buffer, and sets
-// each output bit whose column range of that row holds a set bit (a word-
-// parallel dilation when a = 1).  Then the layer's word prefix and count, as
+// rows, ORs the input rows of their squares into its own row buffer, and
+// dilates and thins that row word-parallel (dilate_row).  Then the layer's word prefix and count, as
 // the layer-by-layer definition gives them.  Every workgroup also clears its
 // share of the next build's input bitmap; workgroups of samples b >= batch only
 // clear.
@@ -245,47 +281,8 @@ __global__ void __launch_bounds__(64) k_rb_bitmaps(RulebookArgs a, int32_t max_w
       row[w] = v;
     }
     if (!live || sub) continue;
-    if (ra == 1) {  // output bit X covers input bits X .. X + rr - 1
-      for (int w = 0; w < Wo; ++w) {
-        const uint64_t lo = row[w], hi = w + 1 < W0 ? row[w + 1] : 0ull;
-        uint64_t acc = lo;
-        for (int d = 1; d < rr; ++d) acc |= (lo >> d) | (hi << (64 - d));
-        out[Y * Wo + w] = acc & row_mask_word(w, So);
-      }
-    } else if (W0 <= 2 && rr <= 64) {  // the input row in registers: bit X = any of bits [a X, a X + rr)
-      const uint64_t r0 = row[0], r1 = W0 > 1 ? row[1] : 0ull;
-      const uint64_t lmask = rr == 64 ? ~0ull : (1ull << rr) - 1ull;
-      for (int w = 0; w < Wo; ++w) {
-        uint64_t acc = 0;
-        const int x_end = min(So, (w + 1) * 64);
-#pragma unroll 4
-        for (int x = w * 64; x < x_end; ++x) {
-          const int lo = ra * x;  // < S0 <= 128; bits past S0 are zero
-          const uint64_t v = lo < 64 ? (r0 >> lo) | (lo ? r1 << (64 - lo) : 0ull) : r1 >> (lo - 64);
-          acc |= ((v & lmask) ? 1ull : 0ull) << (x - w * 64);
-        }
-        out[Y * Wo + w] = acc;
-      }
-    } else {  // output bit X covers input bits [a X, a X + rr)
-      for (int w = 0; w < Wo; ++w) {
-        uint64_t acc = 0;
-        const int x_end = min(So, (w + 1) * 64);
-#pragma unroll 4
-        for (int x = w * 64; x < x_end; ++x) {
-          const int lo = ra * x, hi = min(lo + rr, S0);
-          const int wl = lo >> 6, wh = (hi - 1) >> 6;
-          uint64_t any = 0;
-          for (int q = wl; q <= wh; ++q) {
-            uint64_t v = row[q];
-            if (q == wl) v &= ~0ull << (lo & 63);
-            if (q == wh && (hi & 63)) v &= (1ull << (hi & 63)) - 1ull;
-            any |= v;
-          }
-          acc |= (any ? 1ull : 0ull) << (x - w * 64);
-        }
-        out[Y * Wo + w] = acc;
-      }
-    }
+    dilate_row(row, W0, ra, rr);
+    for (int w = 0; w < Wo; ++w) out[Y * Wo + w] = row[w] & row_mask_word(w, So);
   }
   __syncthreads();
   uint64_t* dst = Lo.bits + (int64_t)b * nwo;
@@ -317,45 +314,51 @@ __global__ void __launch_bounds__(64) k_rb_offsets(RulebookArgs a) {
 // window-list kernel (no separate offsets launch).
 constexpr int LISTS_SCAN_MAX = 1024;
 
-// Exclusive prefixes of up to three count arrays sc[k][0, batch) (null: not
-// scanned) into the LDS arrays off + k * batch, by one workgroup of 256
-// threads (batch <= LISTS_SCAN_MAX): every count is loaded before the first
-// is used.  Returns the total of sc[1] (or of sc[0] when nk == 1).  All threads
-// call it; it synchronises before returning.
-__device__ inline int block_count_scan(const int32_t* const (&sc)[3], int nk, int batch, int* off, int (*wsum)[4]) {
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  const int per = (batch + 255) / 256;  // <= 4
-  const int beg = min(batch, t * per), end = min(batch, beg + per);
-  int c[3][4];
+// Exclusive prefixes of up to NK count arrays sc[k][0, batch) (null: not
+// scanned) by one workgroup of 256 threads (batch <= LISTS_SCAN_MAX), in three
+// steps: the loads, which a caller issues early; the waves' own scans, with their
+// totals to LDS; and, after a barrier, the prefixes into the LDS arrays off + k *
+// batch, returning the total of array KT.  The caller synchronises again before
+// it reads the prefixes.
+template <int NK>
+struct CountScan {
+  int c[NK][4];
+  int run[NK];
+  __device__ inline void load(const int32_t* const (&sc)[NK], int batch) {
+    const int per = (batch + 255) / 256;  // <= 4
+    const int beg = min(batch, (int)threadIdx.x * per), end = min(batch, beg + per);
 #pragma unroll
-  for (int k = 0; k < 3; ++k)
+    for (int k = 0; k < NK; ++k)
 #pragma unroll
-    for (int u = 0; u < 4; ++u) c[k][u] = k < nk && sc[k] && beg + u < end ? sc[k][beg + u] : 0;
-  int run[3];
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    const int local = (c[k][0] + c[k][1]) + (c[k][2] + c[k][3]);
-    int wt;
-    run[k] = wave_exclusive_scan(local, &wt);
-    if (lane == 0) wsum[k][wv] = wt;
+      for (int u = 0; u < 4; ++u) c[k][u] = sc[k] && beg + u < end ? sc[k][beg + u] : 0;
   }
-  __syncthreads();
+  __device__ inline void waves(int (*wsum)[4]) {
 #pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    if (k >= nk || !sc[k]) continue;
-    for (int q = 0; q < wv; ++q) run[k] += wsum[k][q];
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (beg + u < end) {
-        off[k * batch + beg + u] = run[k];
-        run[k] += c[k][u];
-      }
+    for (int k = 0; k < NK; ++k) {
+      const int local = (c[k][0] + c[k][1]) + (c[k][2] + c[k][3]);
+      int wt;
+      run[k] = wave_exclusive_scan(local, &wt);
+      if ((threadIdx.x & 63) == 0) wsum[k][threadIdx.x >> 6] = wt;
+    }
   }
-  const int kt = nk == 1 ? 0 : 1;
-  const int total = (wsum[kt][0] + wsum[kt][1]) + (wsum[kt][2] + wsum[kt][3]);
-  __syncthreads();
-  return total;
-}
+  template <int KT>
+  __device__ inline int finish(int batch, int* off, const int (*wsum)[4]) {
+    const int t = threadIdx.x, wv = t >> 6;
+    const int per = (batch + 255) / 256;
+    const int beg = min(batch, t * per), end = min(batch, beg + per);
+#pragma unroll
+    for (int k = 0; k < NK; ++k) {
+      for (int q = 0; q < wv; ++q) run[k] += wsum[k][q];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (beg + u < end) {
+          off[k * batch + beg + u] = run[k];
+          run[k] += c[k][u];
+        }
+    }
+    return (wsum[KT][0] + wsum[KT][1]) + (wsum[KT][2] + wsum[KT][3]);
+  }
+};
 
 // Row of location (y, x) of sample b in layer L (0 when inactive); off: the
 // sample's offset (sites in earlier samples).
@@ -463,25 +466,32 @@ __device__ inline void row_window_t(const LayerBits& Lo, int b, int y, int x, in
 
 // Rows of every layer, their window lists and transposes, the caller-site ->
 // row map and the head rows, in one launch.  Segment kind 0 (one per layer
-// r): each workgroup takes LISTS_WPB consecutive bitmap words of layer r,
-// eight threads per word, one byte each; the words' sites are listed in LDS
-// in row order (row = 1 + sample offset + word prefix + rank in the word, a
-// block scan over the threads' bytes), then every thread takes listed sites one after
-// another and writes, for its site, the key (sites), R_r and the child ground
-// mask (r >= 1), and the row's entries of Rt_{r+1} (r + 1 < nlayers).  Kind 2:
-// caller site -> input row; kind 3: each sample's top-layer row.  SCAN: every
-// workgroup scans the per-sample counts of the layers it looks up (dynamic
-// LDS: three arrays of batch ints); otherwise the offsets kernel has stored
-// them (soff) and the layer totals.
+// r): each workgroup takes WPB consecutive bitmap words of layer r, 256 / WPB
+// threads per word; the words' sites are listed in LDS in row order (a block scan
+// over the threads' bit counts; LIST_MAX sites at a time), then every thread takes
+// listed sites one after another and writes, for its site (row = 1 + sample
+// offset + word prefix + rank in the word), the key (sites), R_r and the child
+// ground mask (r >= 1), and the row's entries of Rt_{r+1} (r + 1 < nlayers).  Kind
+// 2: caller site -> input row; kind 3: each sample's top-layer row.  SCAN: every
+// workgroup with a site scans the per-sample counts of the layers it looks up
+// (dynamic LDS: three arrays of batch ints); otherwise the offsets kernel has
+// stored them (soff) and the layer totals.
+//
+// Bound at small batches by the chain word -> scan -> lookups of one round of
+// workgroups, at large ones by their number, each with the scan's fixed cost:
+// WPB = 32 while that gives at most a round, else up to 256 (lists_words), and
+// workgroups without a site leave before the scan.
+constexpr int LIST_MAX = 2048;
 
-template <bool SCAN>
+template <bool SCAN, int WPB>
 __global__ void __launch_bounds__(256) k_rb_lists(RulebookArgs a, ListsWork lw) {
-  static_assert(LISTS_WPB * 8 == 256, "eight threads per bitmap word");
+  constexpr int TPW = 256 / WPB, BPT = 64 / TPW;  // threads per word, bits per thread
+  static_assert(TPW * WPB == 256 && TPW * BPT == 64, "whole words");
   extern __shared__ int32_t offs[];  // SCAN: [3][batch], layers r - 1, r, r + 1
-  __shared__ int2 ent[LISTS_WPB * 64];
-  __shared__ int wloc[LISTS_WPB][3];
+  __shared__ int2 ent[LIST_MAX];  // row, word * 64 + bit
+  __shared__ int wloc[WPB][3];    // sample, y, x of bit 0
   __shared__ int wsum[3][4];
-  __shared__ int ntot;
+  __shared__ int wsites[4];
   int seg = 0;
   while (seg + 1 < lw.nseg && (int)blockIdx.x >= lw.blk[seg + 1]) ++seg;
   const int kind = lw.kind[seg], r = lw.layer[seg];
@@ -493,20 +503,38 @@ __global__ void __launch_bounds__(256) k_rb_lists(RulebookArgs a, ListsWork lw) 
     const bool lo = r >= 1, hi = r + 1 < a.nlayers;
     const int per_s = Lr.S * Lr.Wd;  // words per sample (< 2^20)
     const int64_t nwords = (int64_t)B * per_s;
-    const int64_t w0 = (int64_t)bi * LISTS_WPB;
-    // the words and prefixes do not depend on the offsets: loaded first.
-    // Thread t takes bits 8 (t % 8) .. + 7 of word t / 8.
-    const int wi = t >> 3, part = t & 7;
+    const int64_t w0 = (int64_t)bi * WPB;
+    // the words and prefixes do not depend on the offsets: loaded first, then
+    // the counts.  Thread t takes bits BPT (t % TPW) .. of word t / TPW.
+    const int wi = t / TPW, part = t % TPW;
     uint64_t word = 0ull;
     int wp = 0;
     if (w0 + wi < nwords) {
       word = Lr.bits[w0 + wi];
       wp = Lr.wpre[w0 + wi];
     }
-    int tot_r = 0;
+    CountScan<3> cs;
     if constexpr (SCAN) {
       const int32_t* const sc[3] = {lo ? a.L[r - 1].scount : nullptr, Lr.scount, hi ? a.L[r + 1].scount : nullptr};
-      tot_r = block_count_scan(sc, 3, B, offs, wsum);
+      cs.load(sc, B);
+    }
+    // the position of this thread's bits in the workgroup's list: they follow
+    // those of threads < t (a block scan of the per-thread counts)
+    typedef typename std::conditional<(BPT > 32), uint64_t, uint32_t>::type Bits;
+    Bits mine = (Bits)(word >> (BPT * part));
+    if constexpr (BPT < 32) mine &= (1u << BPT) - 1u;
+    int tw;
+    int pre = wave_exclusive_scan(BPT > 32 ? __popcll(mine) : __popc((uint32_t)mine), &tw);
+    if ((t & 63) == 0) wsites[t >> 6] = tw;
+    if constexpr (SCAN) cs.waves(wsum);
+    __syncthreads();
+    for (int q = 0; q < (t >> 6); ++q) pre += wsites[q];
+    const int total = (wsites[0] + wsites[1]) + (wsites[2] + wsites[3]);
+    if (total == 0 && bi != 0) return;
+    int tot_r = 0;
+    if constexpr (SCAN) {
+      tot_r = cs.template finish<1>(B, offs, wsum);
+      __syncthreads();
     }
     auto off_of = [&](int which, int b) -> int32_t {  // which: 0 layer r - 1, 1 layer r, 2 layer r + 1
       if constexpr (SCAN)
@@ -514,15 +542,7 @@ __global__ void __launch_bounds__(256) k_rb_lists(RulebookArgs a, ListsWork lw) 
       else
         return a.L[r - 1 + which].soff[b];
     };
-    // list this workgroup's sites in row order: thread t's bits follow those
-    // of threads < t (a block scan of the per-thread counts)
-    const uint32_t mine = (uint32_t)(word >> (8 * part)) & 0xffu;
-    int tw;
-    int pre = wave_exclusive_scan(__popc(mine), &tw);
-    if ((t & 63) == 0) wsum[0][t >> 6] = tw;
-    __syncthreads();
-    for (int q = 0; q < (t >> 6); ++q) pre += wsum[0][q];
-    if (t == 0) ntot = (wsum[0][0] + wsum[0][1]) + (wsum[0][2] + wsum[0][3]);
+    int row0 = 0;  // row of this thread's first bit
     if (word) {
       const int64_t g = w0 + wi;
       const int b = div_rcp_d(g, per_s);
@@ -533,52 +553,60 @@ __global__ void __launch_bounds__(256) k_rb_lists(RulebookArgs a, ListsWork lw) 
         wloc[wi][1] = y;
         wloc[wi][2] = (rem - y * Lr.Wd) * 64;
       }
-      int row = 1 + off_of(1, b) + wp + __popcll(word & ((1ull << (8 * part)) - 1ull));
-      int k = pre;
-      uint32_t m = mine;
-      while (m) {
-        const int bit = __ffs(m) - 1;
-        m &= m - 1;
-        ent[k++] = make_int2(row++, wi * 64 + 8 * part + bit);
-      }
+      row0 = 1 + off_of(1, b) + wp + __popcll(word & ((1ull << (BPT * part)) - 1ull));
     }
-    __syncthreads();
-    const int total = ntot;
-    for (int i = t; i < total; i += blockDim.x) {
-      const int2 e = ent[i];
-      const int row = e.x, wt = e.y >> 6;
-      const int b = wloc[wt][0], y = wloc[wt][1], x = wloc[wt][2] + (e.y & 63);
-      Lr.sites[row - 1] = (b * Lr.S + y) * Lr.S + x;
-      if (lo) {
-        const LayerBits& Li = a.L[r - 1];
-        const int F = a.F[r], step = a.kind[r] == 1 ? 1 : 2;
-        const int32_t off = off_of(0, b);
-        int32_t* R = a.rules[r] + (int64_t)row * F * F;
-        if (F == 3)
-          row_window<3>(Li, b, y, x, step, off, R);
-        else if (F == 2)
-          row_window<2>(Li, b, y, x, step, off, R);
-        else
-          row_window<1>(Li, b, y, x, step, off, R);
-        if (r >= 2 && a.gmask[r]) a.gmask[r][row] = child_ground_mask(a.L[r - 2], b, y, x);
+    constexpr bool ONE = WPB * 64 <= LIST_MAX;  // every site fits the list
+    for (int l0 = 0; l0 < total; l0 += LIST_MAX) {
+      if (!ONE && l0) __syncthreads();  // the previous sites are done with
+      {
+        int k = pre - l0, row = row0;
+        Bits m = mine;
+        while (m && (ONE || k < LIST_MAX)) {
+          const int bit = BPT > 32 ? __ffsll((unsigned long long)m) - 1 : __ffs((uint32_t)m) - 1;
+          m &= m - 1;
+          if (ONE || k >= 0) ent[k] = make_int2(row, wi * 64 + BPT * part + bit);
+          ++k;
+          ++row;
+        }
       }
-      if (hi) {
-        const LayerBits& Lo = a.L[r + 1];
-        const int32_t off = off_of(2, b);
-        if (a.kind[r + 1] == 1) {
-          const int F = a.F[r + 1];
-          int32_t* Rt = a.rules_t[r + 1] + (int64_t)row * F * F;
+      __syncthreads();
+      const int n = min(total - l0, LIST_MAX);
+      for (int i = t; i < n; i += blockDim.x) {
+        const int2 e = ent[i];
+        const int row = e.x, wt = e.y >> 6;
+        const int b = wloc[wt][0], y = wloc[wt][1], x = wloc[wt][2] + (e.y & 63);
+        Lr.sites[row - 1] = (b * Lr.S + y) * Lr.S + x;
+        if (lo) {
+          const LayerBits& Li = a.L[r - 1];
+          const int F = a.F[r], step = a.kind[r] == 1 ? 1 : 2;
+          const int32_t off = off_of(0, b);
+          int32_t* R = a.rules[r] + (int64_t)row * F * F;
           if (F == 3)
-            row_window_t<3>(Lo, b, y, x, off, Rt);
+            row_window<3>(Li, b, y, x, step, off, R);
           else if (F == 2)
-            row_window_t<2>(Lo, b, y, x, off, Rt);
+            row_window<2>(Li, b, y, x, step, off, R);
           else
-            row_window_t<1>(Lo, b, y, x, off, Rt);
-        } else {  // pooling above: the parent's row times 4 plus the position in its window
-          const int Y = y >> 1, X = x >> 1;
-          int32_t p = -1;
-          if (Y < Lo.S && X < Lo.S) p = rank_row(Lo, b, Y, X, off) * 4 + (y & 1) * 2 + (x & 1);
-          a.rules_t[r + 1][row] = p;
+            row_window<1>(Li, b, y, x, step, off, R);
+          if (r >= 2 && a.gmask[r]) a.gmask[r][row] = child_ground_mask(a.L[r - 2], b, y, x);
+        }
+        if (hi) {
+          const LayerBits& Lo = a.L[r + 1];
+          const int32_t off = off_of(2, b);
+          if (a.kind[r + 1] == 1) {
+            const int F = a.F[r + 1];
+            int32_t* Rt = a.rules_t[r + 1] + (int64_t)row * F * F;
+            if (F == 3)
+              row_window_t<3>(Lo, b, y, x, off, Rt);
+            else if (F == 2)
+              row_window_t<2>(Lo, b, y, x, off, Rt);
+            else
+              row_window_t<1>(Lo, b, y, x, off, Rt);
+          } else {  // pooling above: the parent's row times 4 plus the position in its window
+            const int Y = y >> 1, X = x >> 1;
+            int32_t p = -1;
+            if (Y < Lo.S && X < Lo.S) p = rank_row(Lo, b, Y, X, off) * 4 + (y & 1) * 2 + (x & 1);
+            a.rules_t[r + 1][row] = p;
+          }
         }
       }
     }
@@ -604,8 +632,13 @@ __global__ void __launch_bounds__(256) k_rb_lists(RulebookArgs a, ListsWork lw) 
       x = a.coords[3 * i + 2];
     }
     if constexpr (SCAN) {
-      const int32_t* const sc[3] = {L0.scount, nullptr, nullptr};
-      block_count_scan(sc, 1, B, offs, wsum);
+      const int32_t* const sc[1] = {L0.scount};
+      CountScan<1> cs;
+      cs.load(sc, B);
+      cs.waves(wsum);
+      __syncthreads();
+      cs.template finish<0>(B, offs, wsum);
+      __syncthreads();
     }
     if (i < a.n) {
       int32_t p = -1;
@@ -616,8 +649,13 @@ __global__ void __launch_bounds__(256) k_rb_lists(RulebookArgs a, ListsWork lw) 
   } else {  // each sample's single top-layer site (row 0 when the sample is empty)
     const LayerBits& Lt = a.L[a.nlayers - 1];
     if constexpr (SCAN) {
-      const int32_t* const sc[3] = {Lt.scount, nullptr, nullptr};
-      block_count_scan(sc, 1, B, offs, wsum);
+      const int32_t* const sc[1] = {Lt.scount};
+      CountScan<1> cs;
+      cs.load(sc, B);
+      cs.waves(wsum);
+      __syncthreads();
+      cs.template finish<0>(B, offs, wsum);
+      __syncthreads();
     }
     const int64_t b = (int64_t)bi * blockDim.x + t;
     if (b < B) a.head_rows[b] = rank_row(Lt, (int)b, 0, 0, SCAN ? offs[b] : Lt.soff[b]);
@@ -632,12 +670,23 @@ hipError_t launch_rulebook(const RulebookArgs& a, const ListsWork& lw, int32_t m
   const size_t lds = (size_t)(2 * max_words + 64 * L0.Wd) * sizeof(uint64_t);
   hipLaunchKernelGGL(k_rb_bitmaps, dim3(std::max(a.batch, 1) * a.nlayers), dim3(64), lds, st, a, max_words);
   const bool scan = a.batch >= 1 && a.batch <= LISTS_SCAN_MAX;
-  if (scan) {
-    hipLaunchKernelGGL(k_rb_lists<true>, dim3(lw.blk[lw.nseg]), dim3(256), (size_t)3 * a.batch * sizeof(int32_t), st, a,
-                       lw);
-  } else {
-    hipLaunchKernelGGL(k_rb_offsets, dim3(a.nlayers), dim3(64), 0, st, a);
-    hipLaunchKernelGGL(k_rb_lists<false>, dim3(lw.blk[lw.nseg]), dim3(256), 0, st, a, lw);
+  const size_t slds = scan ? (size_t)3 * a.batch * sizeof(int32_t) : 0;
+  if (!scan) hipLaunchKernelGGL(k_rb_offsets, dim3(a.nlayers), dim3(64), 0, st, a);
+  const dim3 grid(lw.blk[lw.nseg]);
+  switch (lw.words) {
+#define SSCN_LISTS(W)                                                                        \
+  case W:                                                                                    \
+    if (scan)                                                                                \
+      hipLaunchKernelGGL((k_rb_lists<true, W>), grid, dim3(256), slds, st, a, lw);           \
+    else                                                                                     \
+      hipLaunchKernelGGL((k_rb_lists<false, W>), grid, dim3(256), slds, st, a, lw);          \
+    break
+    SSCN_LISTS(32);
+    SSCN_LISTS(64);
+    SSCN_LISTS(128);
+    SSCN_LISTS(256);
+#undef SSCN_LISTS
+    default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }

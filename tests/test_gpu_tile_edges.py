@@ -35,3 +35,28 @@ def test_layers_ending_inside_tiles(case, dtype):
     check_structure(pair)
     check_values(pair)
     assert np.isfinite(pair.loss)
+
+
+# batch, density: 64, 128 and 256 bitmap words per workgroup of the window lists (32 in the cases
+# above), sparse and with more sites in a workgroup's words than its list holds at a time
+@pytest.mark.parametrize("batch,p", [(400, 0.02), (400, 0.9), (900, 0.5), (1024, 0.05), (1600, 0.95), (1600, 0.01)])
+def test_window_lists_of_large_batches(batch, p):
+    ell, k, ncls = 4, 1, 2
+    coords, feats = _sparse_case(950 + batch, ell, batch, p, 1, empty=(0, batch // 2))
+    log(f"[lists] batch {batch} density {p} n={len(coords)}")
+    Ws, bs = he_params(ell, k, 1, ncls, 7)
+    pair = Pair(ell, k, 1, ncls, batch, coords, feats, Ws, bs, random_labels(batch, ncls, 8), "f32")
+    pair.run_gpu()
+    check_structure(pair)
+    # the loss is the sum of every sample's term, several samples to a workgroup above 512
+    np.testing.assert_allclose(pair.loss, pair.o.loss, rtol=1e-5)
+
+
+# depth, side of the sites' box: strided rows of one, two, three and six words
+@pytest.mark.parametrize("ell,p", [(1, 0.4), (5, 0.004), (6, 0.001), (7, 0.0003)])
+def test_bitmaps_of_wide_grids(ell, p):
+    coords, feats = _sparse_case(970 + ell, ell, 3, p, 1)
+    log(f"[bitmaps] ell {ell} n={len(coords)}")
+    Ws, bs = he_params(ell, 1, 1, 2, 7)
+    pair = Pair(ell, 1, 1, 2, 3, coords, feats, Ws, bs, random_labels(3, 2, 8), "f32").run_gpu()
+    check_structure(pair)
