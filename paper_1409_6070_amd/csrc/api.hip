@@ -86,6 +86,7 @@ struct sscn_net {
                   // returned to zero by the kernel that uses them): [1] softmax loss
   int32_t* perm;
   int32_t* head_rows;
+  int32_t* wg_chunks;  // [nconv] site chunks of the weight gradients (ChunkPlan), set by a training forward
   void* dlogits;
   float* dh;
   float* loss_part;
@@ -205,6 +206,7 @@ static void carve(sscn_net* net, void* base) {
   net->err = (int32_t*)cv.take(sizeof(int32_t) * 4);
   net->perm = (int32_t*)cv.take(sizeof(int32_t) * (size_t)net->d.max_active);
   net->head_rows = (int32_t*)cv.take(sizeof(int32_t) * (size_t)B);
+  net->wg_chunks = (int32_t*)cv.take(sizeof(int32_t) * (size_t)net->nconv);
   size_t max_part = 0, max_d0 = 0, max_gpart = 0;
   int max_cp = 0;
   for (int s = 0; s < net->nlayers; ++s) {
@@ -856,7 +858,7 @@ static WGradArgs conv_wgrad_args(const sscn_net* net, int s) {
   w.rows_dev = net->counts + s;
   w.rows_add = 1;
   w.nchunks = P.nchunks;
-  w.slabs = net->wgrad_slabs[P.bn_w == 128 ? 0 : 1];
+  w.nch_dev = net->wg_chunks + ci;
   w.part = net->wpart + P.part_off;
   w.cfg = P.bn_w == 128 ? 0 : 1;
   w.dW = net->dW[ci];
@@ -902,7 +904,7 @@ static hipError_t run_wgrads(sscn_net* net, const WGradArgs* w, int n, hipStream
   if (!fin_done &&
       (e = timed(net, SSCN_KC_GROUND, st, [&] { return launch_extra(net->bf16, *fin, st); })) != hipSuccess)
     return e;
-  return timed(net, SSCN_KC_WGRAD_REDUCE, st, [&] { return launch_wgrad_reduce(net->bf16, w, n, st); });
+  return timed(net, SSCN_KC_WGRAD_REDUCE, st, [&] { return launch_wgrad_reduce(w, n, st); });
 }
 
 // Whether the input-gradient GEMM of convolution s, when it computes the
@@ -1021,6 +1023,22 @@ sscn_status sscn_forward(sscn_net* net, const void* d_feats, const void* const* 
     pa.job[pa.njobs++] = PackJob{h_W[p], P.WpF, 0, P.A, P.c_in, P.c_out, P.cp_in, P.cp_out, P.NpadF, P.KpadF};
     if (train)  // the input-gradient layout is only read by the backward pass
       pa.job[pa.njobs++] = PackJob{h_W[p], P.WpD, 1, P.A, P.c_in, P.c_out, P.cp_in, P.cp_out, P.NpadD, P.KpadD};
+  }
+  if (train) {
+    pa.ch.counts = net->counts;
+    pa.ch.nch = net->wg_chunks;
+    for (int s = 1; s < net->nlayers; ++s) {
+      if (net->L[s].kind != 1) continue;
+      const int ci = net->L[s].conv_index;
+      const ParamPlan& P = net->P[ci];
+      auto& c = pa.ch.L[ci];
+      c.layer = (int16_t)s;
+      c.cfg = P.bn_w == 128 ? 0 : 1;
+      c.nchunks = P.nchunks;
+      c.sites = net->wgrad_slabs[c.cfg] * (net->bf16 ? 64 : 32);
+      c.tiles = (P.Mpad_w / WG_BM) * (P.Npad_w / P.bn_w);
+    }
+    pa.ch.n = net->nconv;
   }
   if (timed(net, SSCN_KC_HEAD, st, [&] { return launch_pack_all(net->bf16, pa, st); }) != hipSuccess)
     return SSCN_ERR_HIP;
@@ -1239,7 +1257,6 @@ sscn_status sscn_backward(sscn_net* net, float* const* h_dW, float* const* h_db,
     f.Npad = P.Npad_w;
     f.rows_host = net->batch;
     f.nchunks = 1;
-    f.slabs = 1;
     f.part = net->wpart;
     f.cfg = P.bn_w == 128 ? 0 : 1;
     f.dW = h_dW[fc];

@@ -332,6 +332,22 @@ __device__ inline void store_pooled(const GemmArgs& a, const T* Cs, const int32_
   }
 }
 
+// Row offset of a window entry that names no row: at or past the end of the
+// source buffer whatever channel is added, so its loads read zero.
+constexpr uint32_t GATHER_NONE = 0x80000000u;
+
+// Chunk c (8 k) of the bf16 GEMM's K: its window position (bits 27..30), its
+// channel's byte offset in the source row (bits 0..26), and GATHER_NONE past K.
+// Looked up per slab instead of divided out: the slab's loads took 45 VALU
+// instructions a thread, a third of all the tile's, against 15.
+__device__ inline int chunk_word(const GemmArgs& a, int c, float rcp_cseg) {
+  const int k = c * 8;
+  if (k >= a.K) return (int)GATHER_NONE;
+  if (a.A == 1) return k * 2;
+  const int f = div_small(k, a.cseg, rcp_cseg);
+  return f << 27 | (k - f * a.cseg) * 2;
+}
+
 // Implicit-gather GEMM.  Per tile: the tile's window rows go to LDS once; the
 // K slabs stream through a ring of LDS stages filled by loads with an LDS
 // destination (bf16: buffer loads, an offset past the buffer reads zero;
@@ -354,7 +370,10 @@ __global__ void __launch_bounds__(C::NT) k_gemm_gather(GemmArgs a) {
   constexpr int LPS = C::AV + C::BV;           // loads per thread and slab
   constexpr int SMEM = NST * STG > BM * CS ? NST * STG : BM * CS;
   __shared__ __attribute__((aligned(16))) T smem[SMEM];
-  extern __shared__ int32_t Rs[];  // [BM * A] window entries, sized at launch
+  // sized at launch: [BM * A] window entries (bf16: the source row's byte offset,
+  // GATHER_NONE where there is none; float32: its row, -1), then (bf16, A > 1) one
+  // word per 16-byte chunk of K, see chunk_word
+  extern __shared__ int32_t Rs[];
   __shared__ int32_t Cr[POOL ? BM : 1];  // pooling forward: the convolution row of each slot
 
   const int tid = threadIdx.x;
@@ -372,9 +391,23 @@ __global__ void __launch_bounds__(C::NT) k_gemm_gather(GemmArgs a) {
   const T* src = (const T*)a.src;
   const T* Bt = (const T*)a.Bt;
   const int A = a.A;
+  const float rcp_cseg = 1.f / (float)a.cseg;
+  const uint32_t row_bytes = (uint32_t)a.src_stride * (uint32_t)sizeof(T);
+  bool tabled = false;
 
   const int grid = own_grid(a.x);
-  for (int tile = blockIdx.x; tile < ntiles; tile += grid) {
+  // Several column tiles to a gathered row tile: consecutive workgroups, which the
+  // hardware deals round-robin to the eight XCDs, take tiles ntiles / 8 apart, so
+  // that a row tile's column tiles and its neighbours read their rows through one
+  // L2.  (DeepCNet(5,50) at batch 1600: 145.6 -> 137.1 us for the third forward,
+  // 225.2 -> 217.9 for the third input gradient; at batch 100 13.9 -> 13.2 and 19.2
+  // -> 18.9.  One column tile, or the softmax layer's few rows, lose by it: 16.2 ->
+  // 16.9, 29.3 -> 48.9.)
+  const bool by_xcd = tiles_n > 1 && a.rmap && a.A > 1 && a.ksplit == 1;
+  const int xcd = by_xcd ? (int)blockIdx.x & 7 : 0, nx = by_xcd ? 8 : 1;
+  const int per_x = (ntiles + nx - 1) / nx;
+  const int tile_end = min(ntiles, (xcd + 1) * per_x), tile_step = (grid + nx - 1 - xcd) / nx;
+  for (int tile = xcd * per_x + (by_xcd ? (int)blockIdx.x >> 3 : (int)blockIdx.x); tile < tile_end; tile += tile_step) {
     const int tn = tile % tiles_n;
     const int t2 = tile / tiles_n;
     const int tm = t2 % tiles_m;
@@ -403,8 +436,18 @@ __global__ void __launch_bounds__(C::NT) k_gemm_gather(GemmArgs a) {
       }
 #pragma unroll
       for (int f = 0; f < AMAX; ++f)
-        if (f < A) Rs[tid * A + f] = live ? v[f] : -1;
+        if (f < A) {
+          if constexpr (sizeof(T) == 2)
+            Rs[tid * A + f] = live && v[f] >= 0 ? v[f] * row_bytes : (int)GATHER_NONE;
+          else
+            Rs[tid * A + f] = live ? v[f] : -1;
+        }
     }
+    if constexpr (sizeof(T) == 2)
+      if (!tabled && A > 1) {  // the same for every tile
+        for (int c = tid; c < a.Kpad / VE; c += NT) Rs[BM * A + c] = chunk_word(a, c, rcp_cseg);
+        tabled = true;
+      }
     __syncthreads();
 
     f32x4 acc[C::TM][C::TN];
@@ -413,7 +456,6 @@ __global__ void __launch_bounds__(C::NT) k_gemm_gather(GemmArgs a) {
 #pragma unroll
       for (int j = 0; j < C::TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    const float rcp_cseg = 1.f / (float)a.cseg;
     // this wave's column blocks below the result's width
     const int live =
         __builtin_amdgcn_readfirstlane((min(a.out_cols - n0, BN) - wn * 16 + 16 * C::WN - 1) / (16 * C::WN));
@@ -424,34 +466,30 @@ __global__ void __launch_bounds__(C::NT) k_gemm_gather(GemmArgs a) {
       const u32x4 rsB = buffer_rsrc(Bt, (uint32_t)a.Npad * (uint32_t)a.Kpad * 2u);
       const int wave_u = __builtin_amdgcn_readfirstlane(wave);  // in a scalar register
       const uint32_t lds0 = lds_addr(smem);
-      const uint32_t row_bytes = (uint32_t)a.src_stride * (uint32_t)sizeof(T);
+      const int chunk = (tid & 7) ^ ((tid >> 4) & 7);
       auto issue = [&](int k0, int st) {
         const uint32_t la = lds0 + (uint32_t)(st * STG * (int)sizeof(T)), lb = la + BM * BK * (int)sizeof(T);
+        // (every slot of a thread holds the same chunk: one window position and
+        // channel per slab)
+        static_assert(NT == 256, "rows 32 apart share their swizzle");
         if constexpr (sizeof(T) == 2) {
+          // (a window of one: K is the row itself, whatever its length)
+          const int w = A > 1 ? Rs[BM * A + k0 / VE + chunk] : chunk_word(a, k0 / VE + chunk, rcp_cseg);
+          const uint32_t col = w & ((1 << 27) - 1), none = w & GATHER_NONE;
+          const int32_t* R = Rs + (tid >> 3) * A + ((w >> 27) & 0xf);
           uint32_t off[C::AV];
 #pragma unroll
-          for (int j = 0; j < C::AV; ++j) {  // every window row read before the first load goes out
-            const int v = tid + j * NT;
-            const int r = v >> 3, c = (v & 7) ^ ((r >> 1) & 7);
-            const int k = k0 + c * VE;
-            const bool in_k = k < a.K;
-            const int f = div_small(k, a.cseg, rcp_cseg);
-            const int srow = Rs[r * A + (in_k ? f : 0)];
-            off[j] = in_k && srow >= 0 ? (uint32_t)(srow * a.src_stride + (k - f * a.cseg)) * 2u : GATHER_SRC_BYTES;
-          }
+          for (int j = 0; j < C::AV; ++j)  // every window row read before the first load goes out
+            off[j] = ((uint32_t)R[j * (NT / 8) * A] + col) | none;
 #pragma unroll
           for (int j = 0; j < C::AV; ++j) dma16(rsA, la + (uint32_t)(wave_u * 64 + j * NT) * 16u, off[j]);
+          const uint32_t bcol = (uint32_t)((n0 + (tid >> 3)) * a.Kpad + k0 + chunk * VE) * 2u;
 #pragma unroll
-          for (int j = 0; j < C::BV; ++j) {
-            const int v = tid + j * NT;
-            const int r = v >> 3, c = (v & 7) ^ ((r >> 1) & 7);
-            dma16(rsB, lb + (uint32_t)(wave_u * 64 + j * NT) * 16u, (uint32_t)((n0 + r) * a.Kpad + k0 + c * VE) * 2u);
-          }
+          for (int j = 0; j < C::BV; ++j)
+            dma16(rsB, lb + (uint32_t)(wave_u * 64 + j * NT) * 16u, bcol + (uint32_t)(j * (NT / 8) * a.Kpad) * 2u);
         } else {
-          // (every slot of a thread holds the same chunk: one window position
-          // and channel per slab; selects, no branches)
-          const int c = (tid & 7) ^ ((tid >> 4) & 7), k = k0 + c * VE;
-          static_assert(NT == 256, "rows 32 apart share their swizzle");
+          // (selects, no branches)
+          const int k = k0 + chunk * VE;
           const bool in_k = k < a.K;
           const int f = div_small(k, a.cseg, rcp_cseg);
           const T* col = src + (k - f * a.cseg);
@@ -535,7 +573,8 @@ __global__ void __launch_bounds__(C::NT) k_gemm_gather(GemmArgs a) {
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             const int ml = wm * C::TM * 16 + i * 16 + g * 4 + r;
-            float v = epi_value<T>(a, acc[i][j][r], bias[j]);
+            // the gradients' epilogues (EPI_STORE, EPI_STORE_MASK) have no bias or rectifier
+            float v = RAC >= 0 || RAC == MASK_MODE ? acc[i][j][r] : epi_value<T>(a, acc[i][j][r], bias[j]);
             if constexpr (RAC == MASK_MODE)  // the rectifier derivative of the layer below,
               if (m0 + ml < rows && n0 + nl < a.out_cols)  // before the one rounding to storage
                 v *= act_factor(
@@ -587,12 +626,11 @@ __global__ void __launch_bounds__(256) k_gemm_splitk_reduce(GemmArgs a) {
   }
 }
 
-// Site chunks actually used: slabs of BK sites per chunk as planned, at most
-// the planned (capacity) chunk count, from the device-side row count.
-__device__ inline int wgrad_chunks_dev(const WGradArgs& a, int rows, int BK) {
-  const int want = (rows + a.slabs * BK - 1) / (a.slabs * BK);
-  return max(1, min(a.nchunks, want));
-}
+// Site chunks of a layer (ChunkPlan; the softmax layer has one).
+__device__ inline int wgrad_chunks(const WGradArgs& a) { return a.nch_dev ? *a.nch_dev : 1; }
+
+// Layers of at least this many chunks have all tiles of a chunk on one XCD.
+constexpr int WG_XCD_CHUNKS = 64;
 
 // A tile's sums for one site chunk.  Several chunks: split-K partials stored
 // as the MFMA result fragments, the layout the reduce reads: per chunk,
@@ -808,17 +846,25 @@ __global__ void __launch_bounds__(C::NT) k_wgrad(WGradGroup grp, ExtraTask x) {
     while (l + 1 < grp.n && t >= grp.tile_beg[l + 1]) ++l;
     const WGradArgs& a = grp.L[l];
     const int tile = t - grp.tile_beg[l];
-    const int rows = a.rows_dev ? (*a.rows_dev + a.rows_add) : a.rows_host;
+    const int rows = a.rows_dev ? *a.rows_dev + a.rows_add : a.rows_host;
     const int tiles_m = a.Mpad / BM, tiles_n = a.Npad / BN;
-    const int nch = wgrad_chunks_dev(a, rows, BK);
+    const int nch = wgrad_chunks(a);
     const int per = ((rows + nch - 1) / nch + BK - 1) / BK * BK;
     const int m_gather = a.A * a.cseg;
     const int m_rows = a.m_ones >= 0 ? a.m_ones + 1 : m_gather;  // rows of dW / db that are read back
-    const int tn = tile % tiles_n;
-    const int tq = tile / tiles_n;
-    const int tm = tq % tiles_m;
-    const int chunk = tq / tiles_m;
+    // Many chunks: all tiles of a chunk on one XCD (workgroups are dealt
+    // round-robin to the eight), chunk c on XCD c % 8, so that its sites' rows,
+    // which every tile of the chunk reads, come through one L2.  Few chunks would
+    // leave XCDs idle.
+    const int tpc = tiles_m * tiles_n;
+    int chunk = tile / tpc, ct = tile - chunk * tpc;
+    if (nch >= WG_XCD_CHUNKS) {
+      const int i = tile >> 3;
+      chunk = i / tpc * 8 + (tile & 7);
+      ct = i - i / tpc * tpc;
+    }
     if (chunk >= nch) continue;  // fewer rows than the plan allowed for
+    const int tm = ct / tiles_n, tn = ct - tm * tiles_n;
     const int m0 = tm * BM, n0 = tn * BN;
     const int o_beg = chunk * per;
     const int o_end = min(rows, o_beg + per);
@@ -854,7 +900,6 @@ __global__ void __launch_bounds__(C::NT) k_wgrad(WGradGroup grp, ExtraTask x) {
         (min(m_rows - m0, BM) - wm * 16 + 16 * C::WM - 1) / (16 * C::WM));
     const int live_n = __builtin_amdgcn_readfirstlane(
         (min(a.c_out - n0, BN) - wn * 16 + 16 * C::WN - 1) / (16 * C::WN));
-    const float rcpA = 1.f / (float)A;
     // window rows of slab s (sites ob .. ob + BKS - 1, A entries each,
     // contiguous) into ring slot s % NST: wave w's i-th load takes dwords
     // 64 k .. 64 k + 63, k = w + 4 i; NRW loads per wave whatever A and s
@@ -866,7 +911,7 @@ __global__ void __launch_bounds__(C::NT) k_wgrad(WGradGroup grp, ExtraTask x) {
         const int k = wave_u + 4 * i;
         const bool used = s < nsl && k < r_loads;
         const int d = 64 * k + lane;
-        const bool live = used && d < BKS * A && ob + div_small(d, A, rcpA) < o_end;
+        const bool live = used && d < BKS * A && ob * A + d < o_end * A;
         const uint32_t to = used ? dst + (uint32_t)k * 256u : lds_spare;
         if constexpr (B16)
           dma4(rsR, to, live ? (uint32_t)(ob * A + d) * 4u : GATHER_SRC_BYTES);
@@ -990,7 +1035,7 @@ __global__ void __launch_bounds__(256) k_wgrad_reduce(WGradGroup grp) {
   int l = 0;
   while (l + 1 < grp.n && (int)blockIdx.x >= grp.blk_beg[l + 1]) ++l;
   const WGradArgs& a = grp.L[l];
-  const int nch = wgrad_chunks_dev(a, a.rows_dev ? (*a.rows_dev + a.rows_add) : a.rows_host, grp.BK);
+  const int nch = wgrad_chunks(a);
   if (nch <= 1) return;  // the weight-gradient kernel wrote the results
   const int G = grp.G[l];
   const int E = 256 / G;  // quads per block
@@ -1049,7 +1094,8 @@ static void launch_cfg(const GemmArgs& a, int64_t max_rows, hipStream_t st) {
                            : !a.route ? k_gemm_gather<T, C, -1>
                            : a.route_ac == 4 ? k_gemm_gather<T, C, 4>
                                              : k_gemm_gather<T, C, 0>;
-  const size_t lds = (size_t)C::BM * a.A * sizeof(int32_t);  // the window table: a workgroup's LDS follows A
+  // the window table and the chunk words: a workgroup's LDS follows A and K
+  const size_t lds = ((size_t)C::BM * a.A + (sizeof(T) == 2 && a.A > 1 ? a.Kpad / C::VE : 0)) * sizeof(int32_t);
   if (timed)
     hipExtLaunchKernelGGL(kern, dim3(grid), dim3(C::NT), lds, st, a.t_start,
                           a.ksplit > 1 && !a.partials_only ? nullptr : a.t_stop, 0, a);
@@ -1085,9 +1131,10 @@ hipError_t launch_gemm(bool bf16, const GemmArgs& args, int64_t max_rows, hipStr
                      !a.pool_out || !a.pool_argmax || !a.rows_dev ||
                      (a.epi != EPI_BIAS_RELU && a.epi != EPI_BIAS_LRELU)))
     return hipErrorInvalidValue;
+  if (a.epi == EPI_STORE_MASK && a.bias) return hipErrorInvalidValue;
   if (a.route) {  // pooling backward in the epilogue: one partial per row tile
     const int bm = gemm_bm(bf16, a.cfg);
-    if (a.epi != EPI_STORE || a.ksplit != 1 || (a.route_ac != 0 && a.route_ac != 4) ||
+    if (a.epi != EPI_STORE || a.bias || a.ksplit != 1 || (a.route_ac != 0 && a.route_ac != 4) ||
         !a.pr.part || !a.pr.Rp || !a.pr.argmax || !a.pr.dZ || !a.pr.X_pool || (a.route_ac == 4 && !a.pr.gmask) ||
         a.pr.cp != a.out_cols || a.pr.stride != a.pr.cp || (max_rows - a.row_begin + bm - 1) / bm > a.pr.PM)
       return hipErrorInvalidValue;
@@ -1189,9 +1236,12 @@ hipError_t launch_wgrad(bool bf16, int cfg, const WGradArgs* layers, int n, hipS
   g.n = n;
   g.tile_beg[0] = 0;
   for (int l = 0; l < n; ++l) {
-    if (layers[l].A < 1 || layers[l].A > AMAX) return hipErrorInvalidValue;
+    if (layers[l].A < 1 || layers[l].A > AMAX || (layers[l].nchunks > 1 && !layers[l].nch_dev))
+      return hipErrorInvalidValue;
     g.L[l] = layers[l];
-    g.tile_beg[l + 1] = g.tile_beg[l] + (layers[l].Mpad / 128) * (layers[l].Npad / BN) * layers[l].nchunks;
+    const int nch = layers[l].nchunks;  // whole groups of eight where chunks may be dealt by XCD
+    g.tile_beg[l + 1] = g.tile_beg[l] + (layers[l].Mpad / 128) * (layers[l].Npad / BN) *
+                                            (nch >= WG_XCD_CHUNKS ? (nch + 7) / 8 * 8 : nch);
   }
   const int grid = std::min(std::max(g.tile_beg[n], 1), device_grid_limit()) + (x.kind ? x.blocks : 0);
   // sites per slab and LDS stages: as many stages as leave two (128 x 128) or
@@ -1210,9 +1260,8 @@ hipError_t launch_wgrad(bool bf16, int cfg, const WGradArgs* layers, int n, hipS
   return hipGetLastError();
 }
 
-hipError_t launch_wgrad_reduce(bool bf16, const WGradArgs* layers, int n, hipStream_t st) {
+hipError_t launch_wgrad_reduce(const WGradArgs* layers, int n, hipStream_t st) {
   WGradGroup g{};
-  g.BK = bf16 ? 64 : 32;
   g.blk_beg[0] = 0;
   for (int l = 0; l < n; ++l) {
     const WGradArgs& a = layers[l];

@@ -49,6 +49,24 @@ __global__ void __launch_bounds__(256) k_gather_dfeats(const T* __restrict__ gra
   }
 }
 
+// ChunkPlan, by one workgroup: a thread per layer.
+__device__ inline void plan_chunks(const ChunkPlan& p) {
+  __shared__ int tiles[2];
+  if (threadIdx.x < 2) tiles[threadIdx.x] = 0;
+  __syncthreads();
+  const int l = threadIdx.x;
+  int rows = 0, cfg = 0;
+  if (l < p.n) {
+    rows = p.counts[p.L[l].layer] + 1;
+    cfg = p.L[l].cfg;
+    atomicAdd(&tiles[cfg], min(p.L[l].nchunks, (rows + p.L[l].sites - 1) / p.L[l].sites) * p.L[l].tiles);
+  }
+  __syncthreads();
+  if (l >= p.n) return;
+  const int64_t per = (int64_t)p.L[l].sites * max(1, (tiles[cfg] + CHUNK_TILES - 1) / CHUNK_TILES);
+  p.nch[l] = max(1, min(p.L[l].nchunks, (int)((rows + per - 1) / per)));
+}
+
 // All weight packings of a step in one launch: one workgroup per tile of 64 n
 // x 32 k of some job's output (tile_beg maps the flat block index to the job).
 //   mode 0 (forward):   Bt[n][f*cp_in + c]  = W[(f*c_in + c)*c_out + n]
@@ -62,7 +80,11 @@ template <typename T>
 __global__ void __launch_bounds__(256) k_pack_all(PackArgs pa) {
   __shared__ T tile[PACK_K][PACK_N + 2];
   const T zero = Elem<T>::from_f32(0.f);
-  const int own = (int)gridDim.x - pa.sc.blocks;
+  const int own = (int)gridDim.x - pa.sc.blocks - (pa.ch.n ? 1 : 0);
+  if (pa.ch.n && (int)blockIdx.x == own + pa.sc.blocks) {
+    plan_chunks(pa.ch);
+    return;
+  }
   if ((int)blockIdx.x >= own) {  // the input scatter's workgroups
     scatter_input_part<T>((const T*)pa.sc.feats, pa.sc.n, pa.sc.c_in, pa.sc.perm, (T*)pa.sc.X0, pa.sc.cp0,
                           (int)blockIdx.x - own, pa.sc.blocks);
@@ -335,7 +357,7 @@ hipError_t launch_pack_all(bool bf16, const PackArgs& in, hipStream_t st) {
   pa.tile_beg[pa.njobs] = (int32_t)total;
   if (pa.sc.X0) pa.sc.blocks = grid_for((int64_t)(pa.sc.n + 1) * (pa.sc.cp0 / (bf16 ? 8 : 4)));
   else pa.sc.blocks = 0;
-  const int grid = (int)std::min<int64_t>(total, 16384) + pa.sc.blocks;  // one tile per workgroup up to 16384
+  const int grid = (int)std::min<int64_t>(total, 16384) + pa.sc.blocks + (pa.ch.n ? 1 : 0);  // one tile per workgroup up to 16384
   if (bf16)
     hipLaunchKernelGGL(k_pack_all<__bf16>, dim3(grid), dim3(256), 0, st, pa);
   else

@@ -9,10 +9,12 @@ namespace sscn {
 
 // Bitmap words of a layer per workgroup of the window-list kernel, for a build of
 // `words` bitmap words in all: 32 (eight threads a word) while that makes at
-// most a round of workgroups (2048 on 256 compute units), else up to 256.
+// most two rounds of workgroups (4096 on 256 compute units), else up to 256.
+// (87k words of dense pictures: 18.0 us with 32 a workgroup, 21.2 with 64; 570k
+// sparse words: 86.0 with 32, 31.0 with 256.)
 inline int lists_words(int64_t words) {
   int w = 32;
-  while (w < 256 && words > (int64_t)w * 2048) w *= 2;
+  while (w < 256 && words > (int64_t)w * 4096) w *= 2;
   return w;
 }
 
@@ -223,8 +225,8 @@ struct WGradArgs {
   const int32_t* rows_dev;
   int32_t rows_add;
   int32_t rows_host;
-  int32_t nchunks;  // planned (most) site chunks; partials hold that many
-  int32_t slabs;    // slabs of sites per chunk: chunks = min(nchunks, rows / (slabs * BK))
+  int32_t nchunks;         // planned (most) site chunks; partials hold that many
+  const int32_t* nch_dev;  // the chunks used (ChunkPlan), null: one
   float* part;
   int32_t cfg;  // 0: 128 x 128 tiles, 1: 128 x 64 tiles
   // with nchunks == 1 the kernel writes the results itself (no partials):
@@ -240,7 +242,6 @@ struct WGradGroup {
   int32_t tile_beg[MAX_WG_LAYERS + 1];  // workgroup tiles of layer l: [tile_beg[l], tile_beg[l+1])
   int32_t blk_beg[MAX_WG_LAYERS + 1];   // reduce blocks of layer l
   int32_t G[MAX_WG_LAYERS];             // reduce thread groups of layer l
-  int32_t BK;                           // sites per slab
   WGradArgs L[MAX_WG_LAYERS];
 };
 
@@ -272,7 +273,7 @@ hipError_t launch_wgrad(bool bf16, int cfg, const WGradArgs* layers, int n, hipS
 
 // part -> dW [A*c_in x c_out] (and db [c_out] when m_ones >= 0) for every layer
 // of the list with nchunks > 1, in one launch.
-hipError_t launch_wgrad_reduce(bool bf16, const WGradArgs* layers, int n, hipStream_t st);
+hipError_t launch_wgrad_reduce(const WGradArgs* layers, int n, hipStream_t st);
 // grad_in[0][c] = sum_f sum_n W[(f*c_in + c)*c_out + n] * D0[f][n], times
 // act_factor(Y_below[0][c], slope) when Y_below (the layer below's stored
 // output, a convolution) is given
@@ -326,12 +327,31 @@ struct ScatterArgs {
   int32_t cp0;
   int32_t blocks;  // workgroups given to it (0: no scatter)
 };
+// The site chunks of the weight gradients, from the device-side row counts: per
+// layer, `sites` a chunk as planned, and the same multiple of that for all layers
+// of a tile width that brings their tiles down to CHUNK_TILES (two to three rounds
+// of resident workgroups; more tiles only multiply the partial sums, which
+// DeepCNet(5,50) at batch 1600 wrote and read back 314 MB of: weight gradients and
+// reduce 537 -> 450 us); at most the planned chunk count.  Worked out once a pass,
+// by one workgroup of the packing launch.
+constexpr int CHUNK_TILES = 1536;
+struct ChunkPlan {
+  int32_t n;
+  const int32_t* counts;  // active sites per layer
+  int32_t* nch;           // [n], the result
+  struct {
+    int16_t layer, cfg;  // row count: counts[layer] + 1; tile width (WGradArgs::cfg)
+    int32_t nchunks, sites, tiles;  // planned chunks, sites per chunk, tiles per chunk
+  } L[MAX_WG_LAYERS];
+};
 struct PackArgs {
   int32_t njobs;
   int32_t tile_beg[2 * MAX_LAYERS + 1];  // first tile of each job in the flat tile range (set by the launcher)
   PackJob job[2 * MAX_LAYERS];
   ScatterArgs sc;
+  ChunkPlan ch;  // n == 0: none
 };
+static_assert(sizeof(PackArgs) <= 4096, "kernel arguments must fit the 4 KiB argument segment");
 // All packings of a step (and, with sc.feats or sc.n == 0 and sc.X0 set, the
 // input scatter) in one launch.
 hipError_t launch_pack_all(bool bf16, const PackArgs& pa, hipStream_t st);

@@ -110,37 +110,62 @@ __device__ inline void route_apply(const GroundArgs& g, int c, const RouteIn<T, 
                                    float (&acc)[2 + AC][Elem<T>::VE]) {
   constexpr int VE = Elem<T>::VE;
   T* dZ = (T*)g.dZ;
-  // bit f: child f is the ground row; bit AC f + k: child f's window position k reads it
-  const uint32_t gch = (q.r[0] == 0 ? 1u : 0u) | (q.r[1] == 0 ? 2u : 0u) | (q.r[2] == 0 ? 4u : 0u) |
-                       (q.r[3] == 0 ? 8u : 0u);
-  uint64_t gw = 0;
+  // byte f: child f of the window; bits 0..3 (AC == 4) its window positions that
+  // read the ground row, bit 4 set when it is an active row itself
+  uint32_t child = (q.r[0] != 0 ? 0x10u : 0u) | (q.r[1] != 0 ? 0x1000u : 0u) | (q.r[2] != 0 ? 0x100000u : 0u) |
+                   (q.r[3] != 0 ? 0x10000000u : 0u);
   if constexpr (AC == 4) {
-    gw = q.cw.gm;
-  } else if constexpr (AC > 0) {
+    const uint32_t m = q.cw.gm;
+    child |= (m & 0xfu) | (m & 0xf0u) << 4 | (m & 0xf00u) << 8 | (m & 0xf000u) << 12;
+  }
+  uint64_t gw = 0;  // other AC: bit AC f + k, child f's window position k reads the ground row
+  if constexpr (AC != 0 && AC != 4) {
 #pragma unroll
     for (int f = 0; f < 4; ++f)
 #pragma unroll
       for (int k = 0; k < AC; ++k) gw |= (uint64_t)(q.cw.wr[f].v[k] == 0 ? 1u : 0u) << (AC * f + k);
   }
+  // Bound by its vector instructions (about 55 a value as selects on compared
+  // positions, 32 like this): the chosen child's flags are shifted down, turned
+  // into all-ones masks and ANDed, and each child's share of a word of output is cut
+  // out with byte masks (byte f of an element's word all ones for its child f).
+  const uint32_t am8[2] = {(uint32_t)q.am << 3, (uint32_t)((uint64_t)q.am >> 32) << 3};  // 8 x position, a byte each
+  auto mask = [](uint32_t v, int bit) { return (uint32_t)((int32_t)(v << (31 - bit)) >> 31); };
   ru32x4 out[4];
-  // every sum is updated on both branches (a select, not a branch), so that
-  // the accumulators stay in registers
+  uint32_t pick[VE];  // byte f all ones when child f takes element j
 #pragma unroll
   for (int j = 0; j < VE; ++j) {
-    const int a = (int)((q.am >> (8 * j)) & 3);
+    const uint32_t sh = (am8[j / 4] >> (8 * (j % 4))) & 31u;
+    const uint32_t t = child >> sh;
+    pick[j] = 0xffu << sh;
     const float gj = Elem<T>::to_f32(gv[j]);
     const T o = Elem<T>::from_f32(gj * act_factor(Elem<T>::to_f32(((const T*)&q.xp)[j]), g.slope));
-    const bool ground = (gch >> a) & 1u;
-    const float d = ground ? 0.f : Elem<T>::to_f32(o);
-    acc[0][j] += ground ? gj : 0.f;
-    acc[1][j] += d;
-    if constexpr (AC > 0) {
-      const uint64_t ga = gw >> (AC * a);
+    ((T*)&out[0])[j] = o;
+    const uint32_t on = mask(t, 4);
+    const uint32_t db = __float_as_uint(Elem<T>::to_f32(o)) & on;
+    acc[0][j] += __uint_as_float(__float_as_uint(gj) & ~on);
+    acc[1][j] += __uint_as_float(db);
+    if constexpr (AC == 4) {
 #pragma unroll
-      for (int k = 0; k < AC; ++k) acc[2 + k][j] += ((ga >> k) & 1u) ? d : 0.f;
+      for (int k = 0; k < AC; ++k) acc[2 + k][j] += __uint_as_float(db & mask(t, k));
+    } else if constexpr (AC > 0) {
+      const uint64_t ga = gw >> (AC * (sh >> 3));
+#pragma unroll
+      for (int k = 0; k < AC; ++k) acc[2 + k][j] += ((ga >> k) & 1u) ? __uint_as_float(db) : 0.f;
     }
+  }
 #pragma unroll
-    for (int f = 0; f < 4; ++f) ((T*)&out[f])[j] = a == f ? o : Elem<T>::from_f32(0.f);
+  for (int w = 0; w < 4; ++w) {
+    const uint32_t all = out[0][w];
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+      uint32_t m;
+      if constexpr (VE == 8)  // two elements: byte f of each, twice
+        m = __builtin_amdgcn_perm(pick[2 * w + 1], pick[2 * w], (0x04040000u | 0x01010101u * f));
+      else
+        m = __builtin_amdgcn_perm(0u, pick[w], 0x01010101u * f);
+      out[f][w] = all & m;
+    }
   }
 #pragma unroll
   for (int f = 0; f < 4; ++f)
