@@ -432,10 +432,11 @@ sscn_status sscn_net_create(const sscn_net_desc* desc, sscn_net** out) {
     P.rows_d = L[s - 1].cap + 1;
     // a convolution under a pooling layer computes that layer in its epilogue
     const bool pooled = s + 1 < net->nlayers && L[s + 1].kind == 2;
-    P.pf = plan_gemm(net->bf16, P.rows_f, P.c_out, P.A * P.cp_in, false, pooled ? 256 : 128);
+    P.pf = plan_gemm(net->bf16, P.rows_f, P.c_out, P.A * P.cp_in, pooled ? GEMM_POOLED : GEMM_PLAIN);
     // an input gradient that is a pooling layer's may route its rows through the
     // pooling windows in its epilogue
-    P.pd = plan_gemm(net->bf16, P.rows_d, P.c_in, P.A * P.cp_out, L[s - 1].kind == 2, 600);
+    P.pd = plan_gemm(net->bf16, P.rows_d, P.c_in, P.A * P.cp_out,
+                     L[s - 1].kind == 2 ? GEMM_ROUTED : GEMM_PLAIN);
     P.NpadF = P.pf.Npad;
     P.KpadF = P.pf.Kpad;
     P.NpadD = P.pd.Npad;
@@ -474,8 +475,8 @@ sscn_status sscn_net_create(const sscn_net_desc* desc, sscn_net** out) {
     P.cp_out = net->dl_stride;
     P.rows_f = d.batch_max;
     P.rows_d = d.batch_max;
-    P.pf = plan_gemm(net->bf16, P.rows_f, P.c_out, P.cp_in, false, 128);
-    P.pd = plan_gemm(net->bf16, P.rows_d, P.c_in, P.cp_out, false, 128);
+    P.pf = plan_gemm(net->bf16, P.rows_f, P.c_out, P.cp_in, GEMM_PLAIN);
+    P.pd = plan_gemm(net->bf16, P.rows_d, P.c_in, P.cp_out, GEMM_PLAIN);
     P.NpadF = P.pf.Npad;
     P.KpadF = P.pf.Kpad;
     P.NpadD = P.pd.Npad;
@@ -1351,8 +1352,8 @@ static size_t encode_bytes(int64_t N, int64_t batch, int64_t max_sites, size_t* 
   offs[1] = take(words * 4);            // wpre
   offs[2] = take(batch * 4);            // scount
   offs[3] = take(batch * 4);            // soff
-  offs[4] = take(4);                    // total
-  offs[5] = take(4);                    // err
+  offs[4] = take(8);                    // total, error word
+  offs[5] = take(4);                    // (unused; the size stays what callers have been told)
   offs[6] = take(max_sites * 8 * 4);    // counts
   return off + 256;
 }
@@ -1419,15 +1420,13 @@ static sscn_status encode_strokes(int32_t N, int32_t dtype, const int32_t* d_poi
   a.wpre = (int32_t*)(base + offs[1]);
   a.scount = (int32_t*)(base + offs[2]);
   a.soff = (int32_t*)(base + offs[3]);
-  a.total = (int32_t*)(base + offs[4]);
-  a.err = (int32_t*)(base + offs[5]);
+  a.total = (int32_t*)(base + offs[4]);  // [0] the count, [1] the error word: read back together
   a.counts = (int32_t*)(base + offs[6]);
   a.coords = d_coords;
   hipStream_t st = (hipStream_t)stream;
   if (launch_encode(dtype == SSCN_BF16, a, d_feats, st) != hipSuccess) return SSCN_ERR_HIP;
   int32_t res[2] = {0, 0};
-  if (hipMemcpyAsync(&res[0], a.total, 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
-      hipMemcpyAsync(&res[1], a.err, 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
+  if (hipMemcpyAsync(res, a.total, sizeof(res), hipMemcpyDeviceToHost, st) != hipSuccess ||
       hipStreamSynchronize(st) != hipSuccess)
     return SSCN_ERR_HIP;
   *h_count = res[0];

@@ -49,25 +49,30 @@ __device__ inline int stroke_of(const int32_t* begin, int n_strokes, int t) {
 
 __device__ inline bool in_grid(int y, int x, int N) { return (unsigned)y < (unsigned)N && (unsigned)x < (unsigned)N; }
 
-__global__ void __launch_bounds__(256) k_enc_clear(uint32_t* p, int64_t words) {
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < words; t += (int64_t)gridDim.x * blockDim.x)
-    p[t] = 0u;
+// Clears the bitmap and the move counts (16 bytes a thread and round; both arrays
+// are 256-byte aligned), the total and the error word.
+typedef uint32_t enc4u __attribute__((ext_vector_type(4)));
+__global__ void __launch_bounds__(256) k_enc_clear(EncodeArgs a) {
+  const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
+  const int64_t words = (int64_t)a.batch * a.N * a.Wd, quads = words / 2, counts = (int64_t)a.max_sites * 2;
+  for (int64_t t = t0; t < quads; t += stride) ((enc4u*)a.bits)[t] = enc4u{0u, 0u, 0u, 0u};
+  for (int64_t t = t0; t < counts; t += stride) ((enc4u*)a.counts)[t] = enc4u{0u, 0u, 0u, 0u};
+  if (t0 == 0 && (words & 1)) a.bits[words - 1] = 0ull;
+  if (t0 < 2) a.total[t0] = 0;
 }
 
 // Offsets and samples are valid: begin runs from 0 to n_points, non-decreasing;
 // every stroke's sample lies in the batch.
-__global__ void __launch_bounds__(256) k_enc_check(EncodeArgs a) {
-  for (int s = blockIdx.x * blockDim.x + threadIdx.x; s <= a.n_strokes; s += gridDim.x * blockDim.x) {
-    const int b0 = a.begin[s];
-    bool ok = b0 >= 0 && b0 <= a.n_points;
-    if (s == 0) ok = ok && b0 == 0;
-    if (s == a.n_strokes) ok = ok && b0 == a.n_points;
-    if (s < a.n_strokes) {
-      ok = ok && a.begin[s + 1] >= b0;
-      if ((unsigned)a.sample[s] >= (unsigned)a.batch) atomicOr(a.err, ERRBIT_RANGE);
-    }
-    if (!ok) atomicOr(a.err, ERRBIT_ORDER);
+__device__ inline void check_stroke(const EncodeArgs& a, int s) {
+  const int b0 = a.begin[s];
+  bool ok = b0 >= 0 && b0 <= a.n_points;
+  if (s == 0) ok = ok && b0 == 0;
+  if (s == a.n_strokes) ok = ok && b0 == a.n_points;
+  if (s < a.n_strokes) {
+    ok = ok && a.begin[s + 1] >= b0;
+    if ((unsigned)a.sample[s] >= (unsigned)a.batch) atomicOr(&a.total[1], ERRBIT_RANGE);
   }
+  if (!ok) atomicOr(&a.total[1], ERRBIT_ORDER);
 }
 
 // Segment t -> t + 1 of its stroke (or the lone last point), validated; returns
@@ -83,7 +88,7 @@ __device__ inline bool load_segment(const EncodeArgs& a, int t, Seg& g) {
   g.y0 = a.points[2 * t];
   g.x0 = a.points[2 * t + 1];
   if (!in_grid(g.y0, g.x0, a.N)) {
-    atomicOr(a.err, ERRBIT_RANGE);
+    atomicOr(&a.total[1], ERRBIT_RANGE);
     return false;
   }
   g.dy = g.dx = g.L = 0;
@@ -98,8 +103,11 @@ __device__ inline bool load_segment(const EncodeArgs& a, int t, Seg& g) {
   return true;
 }
 
-// Marks pixels 0 .. L-1 of every segment and the last point of every stroke.
+// Checks every stroke; marks pixels 0 .. L-1 of every segment and the last point
+// of every stroke.
 __global__ void __launch_bounds__(256) k_enc_mark(EncodeArgs a) {
+  for (int s = blockIdx.x * blockDim.x + threadIdx.x; s <= a.n_strokes; s += gridDim.x * blockDim.x) check_stroke(a, s);
+  if (a.n_strokes == 0) return;
   for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < a.n_points; t += gridDim.x * blockDim.x) {
     Seg g;
     if (!load_segment(a, t, g)) continue;
@@ -142,32 +150,6 @@ __global__ void __launch_bounds__(ENC_THREADS) k_enc_prefix(EncodeArgs a) {
   if (t == ENC_THREADS - 1) a.scount[b] = scratch[ENC_THREADS - 1];
 }
 
-// Sample offsets (exclusive scan of the counts) and the total, one workgroup.
-__global__ void __launch_bounds__(ENC_THREADS) k_enc_offsets(EncodeArgs a) {
-  __shared__ int scratch[ENC_THREADS];
-  const int t = threadIdx.x;
-  const int per = (a.batch + ENC_THREADS - 1) / ENC_THREADS;
-  const int beg = t * per;
-  int local = 0;
-  for (int j = 0; j < per; ++j)
-    if (beg + j < a.batch) local += a.scount[beg + j];
-  scratch[t] = local;
-  __syncthreads();
-  for (int off = 1; off < ENC_THREADS; off <<= 1) {
-    const int v = t >= off ? scratch[t - off] : 0;
-    __syncthreads();
-    scratch[t] += v;
-    __syncthreads();
-  }
-  int run = scratch[t] - local;
-  for (int j = 0; j < per; ++j)
-    if (beg + j < a.batch) {
-      a.soff[beg + j] = run;
-      run += a.scount[beg + j];
-    }
-  if (t == ENC_THREADS - 1) a.total[0] = scratch[ENC_THREADS - 1];
-}
-
 // Row (0-based) of the marked pixel (b, y, x).
 __device__ inline int enc_row(const EncodeArgs& a, int b, int y, int x) {
   const int64_t idx = ((int64_t)b * a.N + y) * a.Wd + (x >> 6);
@@ -175,17 +157,30 @@ __device__ inline int enc_row(const EncodeArgs& a, int b, int y, int x) {
   return a.soff[b] + a.wpre[idx] + __popcll(below);
 }
 
-// Sites in ascending (b, y, x) order, the first max_sites of them.
-__global__ void __launch_bounds__(256) k_enc_sites(EncodeArgs a) {
+// Sites in ascending (b, y, x) order, the first max_sites of them: workgroup b
+// takes sample b's words, after summing the counts of the samples before it for
+// its offset (the last sample's gives the total).
+__global__ void __launch_bounds__(ENC_THREADS) k_enc_sites(EncodeArgs a) {
+  __shared__ int part[ENC_THREADS / 64];
+  const int b = blockIdx.x, t = threadIdx.x;
+  int sum = 0;
+#pragma unroll 4
+  for (int i = t; i < b; i += ENC_THREADS) sum += a.scount[i];
+  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+  if ((t & 63) == 0) part[t >> 6] = sum;
+  __syncthreads();
+  const int off = (part[0] + part[1]) + (part[2] + part[3]);
+  if (t == 0) {
+    a.soff[b] = off;
+    if (b == a.batch - 1) a.total[0] = off + a.scount[b];
+  }
   const int nw = a.N * a.Wd;
-  const int64_t words = (int64_t)a.batch * nw;
-  for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < words; g += (int64_t)gridDim.x * blockDim.x) {
+  for (int rem = t; rem < nw; rem += ENC_THREADS) {
+    const int64_t g = (int64_t)b * nw + rem;
     uint64_t w = a.bits[g];
     if (!w) continue;
-    const int b = (int)(g / nw);
-    const int rem = (int)(g - (int64_t)b * nw);
     const int y = rem / a.Wd, wx = rem - y * a.Wd;
-    int row = a.soff[b] + a.wpre[g];
+    int row = off + a.wpre[g];
     while (w) {
       const int bit = __ffsll((long long)w) - 1;
       w &= w - 1;
@@ -238,22 +233,15 @@ __global__ void __launch_bounds__(256) k_enc_feats(EncodeArgs a, T* feats) {
 
 static int enc_grid(int64_t items) { return (int)std::max<int64_t>(1, std::min<int64_t>((items + 255) / 256, 4096)); }
 
+// Six launches (ten with the clears, the check and the offsets as their own: 33 us
+// of kernels for 100 pen paths, 22 like this), each a few dependent loads long.
 hipError_t launch_encode(bool bf16, const EncodeArgs& a, void* feats, hipStream_t st) {
   const int64_t words = (int64_t)a.batch * a.N * a.Wd;
-  // bitmap words and move counts start at zero; so does the error word
-  hipLaunchKernelGGL(k_enc_clear, dim3(enc_grid(2 * words)), dim3(256), 0, st, (uint32_t*)a.bits, 2 * words);
-  hipLaunchKernelGGL(k_enc_clear, dim3(enc_grid((int64_t)a.max_sites * 8)), dim3(256), 0, st, (uint32_t*)a.counts,
-                     (int64_t)a.max_sites * 8);
-  hipLaunchKernelGGL(k_enc_clear, dim3(1), dim3(256), 0, st, (uint32_t*)a.err, (int64_t)1);
-  hipLaunchKernelGGL(k_enc_check, dim3(enc_grid(a.n_strokes + 1)), dim3(256), 0, st, a);
-  if (a.n_points > 0 && a.n_strokes > 0)
-    hipLaunchKernelGGL(k_enc_mark, dim3(enc_grid(a.n_points)), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(k_enc_clear, dim3(enc_grid(std::max(words / 2, (int64_t)a.max_sites * 2))), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(k_enc_mark, dim3(enc_grid(std::max(a.n_points, a.n_strokes + 1))), dim3(256), 0, st, a);
   if (a.batch > 0) {
     hipLaunchKernelGGL(k_enc_prefix, dim3(a.batch), dim3(ENC_THREADS), 0, st, a);
-    hipLaunchKernelGGL(k_enc_offsets, dim3(1), dim3(ENC_THREADS), 0, st, a);
-    hipLaunchKernelGGL(k_enc_sites, dim3(enc_grid(words)), dim3(256), 0, st, a);
-  } else {
-    hipLaunchKernelGGL(k_enc_clear, dim3(1), dim3(256), 0, st, (uint32_t*)a.total, (int64_t)1);
+    hipLaunchKernelGGL(k_enc_sites, dim3(a.batch), dim3(ENC_THREADS), 0, st, a);
   }
   if (a.n_points > 0 && a.n_strokes > 0 && a.batch > 0)
     hipLaunchKernelGGL(k_enc_moves, dim3(enc_grid(a.n_points)), dim3(256), 0, st, a);

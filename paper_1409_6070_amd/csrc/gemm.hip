@@ -1147,17 +1147,21 @@ hipError_t launch_gemm(bool bf16, const GemmArgs& args, int64_t max_rows, hipStr
   return hipGetLastError();
 }
 
-GemmPlan plan_gemm(bool bf16, int64_t max_rows, int N, int K, bool short_rows, int direct_max) {
+GemmPlan plan_gemm(bool bf16, int64_t max_rows, int N, int K, GemmKind kind) {
+  const bool short_rows = kind == GEMM_ROUTED;
   // Launches with few output tiles (at the row bound) go to the
   // direct-operand kernel, whose waves split K and so keep many loads in flight
   // per tile; launches with more tiles keep the LDS-tiled kernel, whose slabs
   // stream through LDS stages shared by the tile's waves.  (Measured on the
   // pen-stroke DeepCNet(5,50), bf16, batch 100, tiles counted as 32 x 64 at the
-  // row bound: input gradients with the pooling backward, direct 18.7 us against
-  // 19.6 us at 316 tiles, but 24.1 against 20.4 at 1.1k and 31.1 against 20.9
-  // at 3.3k; forward with the pooling forward even at 204 tiles; the softmax
-  // layer's forward, 236 tiles, 7.2 us direct against 6.6 LDS-tiled.  The
-  // callers pass 600, 256 and 128.)
+  // row bound: forward with the pooling forward, 204 tiles, 10.0 us direct against
+  // 12.0 LDS-tiled; the softmax layer's forward, 236 tiles, 7.2 us direct against
+  // 6.6 LDS-tiled.  Input gradients with the pooling backward, K 1200 at 52 tiles
+  // 12.5 us direct against 7.6 with a split-K reduce and a pooling pass (4.5 + 7.5)
+  // behind it, K 1000 at 364 tiles 18.9 against 16.1, but K 160 at 420 tiles 8.5
+  // against 9.4: up to 256 tiles, or 600 for K <= 320.  The last convolution's
+  // forward, 20 tiles of K 1000, 10.2 us direct against 5.7 with a reduce of 4.6;
+  // 50 tiles of K 2000 15.1 against 8.0 and 4.6: split K above 1024.)
   // float32 (one lane holds 4 k, not 8: twice the loads per k block and sixteen
   // times the MFMA time) goes there for up to 128 tiles and K <= 512, where it
   // saves the split-K reduce and lets the pooling passes ride in the epilogue:
@@ -1165,9 +1169,12 @@ GemmPlan plan_gemm(bool bf16, int64_t max_rows, int N, int K, bool short_rows, i
   // (pooling) -> 7.5 us, input gradients 7.0 + 3.7 + 4.8 -> 13.7 us; but K = 1000
   // at 20 tiles 20.1 us against 6.7 + 5.0.
   const int64_t direct_tiles = ((max_rows + DIRECT_BM - 1) / DIRECT_BM) * ((N + DIRECT_BN - 1) / DIRECT_BN);
-  if (direct_tiles <= (bf16 ? direct_max : 128) && K <= (bf16 ? 2048 : 512)) {
-    // waves per tile so that each sums at most about four k blocks (32 wide, 16
-    // for float32), and more while the grid stays small
+  const int64_t most = !bf16 ? 128 : kind == GEMM_ROUTED ? (K <= 320 ? 600 : 256) : kind == GEMM_POOLED ? 256 : 128;
+  if (direct_tiles <= most && K <= (!bf16 ? 512 : kind == GEMM_PLAIN ? 1024 : 2048)) {
+    // four waves per tile while the grid stays small (their number also sets the
+    // threads of the epilogue: a window of one over 16 k, 40 tiles: 11.2 us with
+    // one wave), else as many as leave each about four k blocks (32 wide, 16 for
+    // float32)
     GemmPlan p;
     p.cfg = GEMM_DIRECT;
     p.BN = DIRECT_BN;
@@ -1178,7 +1185,7 @@ GemmPlan plan_gemm(bool bf16, int64_t max_rows, int N, int K, bool short_rows, i
     const int64_t tiles = ((max_rows + DIRECT_BM - 1) / DIRECT_BM) * (p.Npad / DIRECT_BN);
     int sk = 1;
     while (sk < 4 && sk * 4 < ksteps) sk *= 2;
-    while (sk < 4 && sk * 2 <= ksteps && tiles * sk < 4096) sk *= 2;
+    while (sk < 4 && tiles * sk < 4096) sk *= 2;
     p.sk = sk;
     return p;
   }

@@ -249,7 +249,10 @@ struct GemmTile {
   int BM, BN, BK;
 };
 GemmTile gemm_tile(bool bf16, int cfg);
-GemmPlan plan_gemm(bool bf16, int64_t max_rows, int N, int K, bool short_rows, int direct_max);
+// What a launch's epilogue does: nothing more, the pooling forward above it, or
+// (an input gradient that is a pooling layer's) the pooling backward below it.
+enum GemmKind { GEMM_PLAIN, GEMM_POOLED, GEMM_ROUTED };
+GemmPlan plan_gemm(bool bf16, int64_t max_rows, int N, int K, GemmKind kind);
 // weight-gradient tiles: 128 rows of dW, 128 or 64 columns
 constexpr int WG_BM = 128;
 inline int wgrad_bn(int c_out) { return (c_out + 127) / 128 * 128 <= (c_out + 63) / 64 * 64 ? 128 : 64; }
@@ -409,8 +412,7 @@ struct EncodeArgs {
   int32_t* wpre;     // [batch][N][Wd] exclusive popcount prefix within the sample
   int32_t* scount;   // [batch]
   int32_t* soff;     // [batch]
-  int32_t* total;    // [1] distinct sites
-  int32_t* err;      // [1] ERRBIT_*
+  int32_t* total;    // [0] distinct sites, [1] ERRBIT_*
   int32_t* counts;   // [max_sites][8] move counts
   int32_t* coords;   // [max_sites][3] output
 };
