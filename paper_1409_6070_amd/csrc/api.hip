@@ -192,11 +192,24 @@ static int64_t route_tiles(const sscn_net* net, int s, int* bm) {
   if (s < 3) return 0;
   const LayerPlan& L = net->L[s];
   const LayerPlan& Lp = net->L[s - 1];
-  if (L.kind != 1 || Lp.kind != 2 || net->L[s - 2].kind != 1 || L.A < 2) return 0;
+  if (L.kind != 1 || Lp.kind != 2 || net->L[s - 2].kind != 1) return 0;
   const ParamPlan& P = net->P[L.conv_index];
   if (P.pd.ksplit != 1) return 0;
   *bm = gemm_bm(net->bf16, P.pd.cfg);
   return (Lp.cap + *bm - 1) / *bm;  // rows 1 .. cap
+}
+
+// Row tiles at capacity (and their height) of the input-gradient GEMM of
+// convolution s when it writes the delta of a 1x1 layer s-1 with that layer's bias
+// sums, one partial per row tile; 0 otherwise.
+static int64_t sum_tiles(const sscn_net* net, int s, int* bm) {
+  const LayerPlan& L = net->L[s];
+  const LayerPlan& Lb = net->L[s - 1];
+  if (L.kind != 1 || Lb.kind != 1 || Lb.A != 1) return 0;
+  const ParamPlan& P = net->P[L.conv_index];
+  if (P.pd.ksplit != 1) return 0;
+  *bm = gemm_bm(net->bf16, P.pd.cfg);
+  return (Lb.cap + *bm - 1) / *bm;  // rows 1 .. cap
 }
 
 static void carve(sscn_net* net, void* base) {
@@ -273,6 +286,8 @@ static void carve(sscn_net* net, void* base) {
     int bm = 0;
     const int64_t t = route_tiles(net, s, &bm);
     if (t > 0) net->ppart_half = std::max(net->ppart_half, (size_t)(2 + 4) * net->L[s - 2].Cp * (size_t)t);
+    const int64_t u = sum_tiles(net, s, &bm);
+    if (u > 0) net->ppart_half = std::max(net->ppart_half, (size_t)2 * net->L[s - 1].Cp * (size_t)u);
   }
   net->ppart = (float*)cv.take(2 * net->ppart_half * 4);
   net->hdrop = net->d.dropout ? cv.take((size_t)B * Lt.Cp * net->esz) : nullptr;
@@ -795,7 +810,7 @@ static hipError_t ground_level(sscn_net* net, int s, bool pool_above, hipStream_
   const LayerPlan& Lb = net->L[s - 1];
   const int ci = L.conv_index;
   const ParamPlan& P = net->P[ci];
-  // a 1x1 layer's input-gradient GEMM covers row 0 itself (its window is the row)
+  // (here a 1x1 layer's input-gradient GEMM covers row 0 itself: its window is the row)
   const bool row0 = needs_row0(net, s) && L.A > 1;
   const GroundArgs g = ground_args(net, s, pool_above);
   hipError_t e;
@@ -820,6 +835,7 @@ static ExtraTask final_task(const sscn_net* net, int s, bool pool_above) {
   x.blocks = L.Cp;
   x.AC = (needs_row0(net, s) && L.A > 1) ? L.A : 0;
   x.g = ground_args(net, s, pool_above);
+  x.g.d0_row = needs_row0(net, s) && L.A == 1;
   return x;
 }
 
@@ -931,12 +947,14 @@ static bool route_into(const sscn_net* net, int s, int* ac, int* bm, int* tiles)
 // Rows >= 1 of the gradient below stage s: the pooling backward (with the
 // partial sums of the convolution below), or the input-gradient GEMM of a
 // convolution.  (The GEMM reads delta rows >= 1 only: a window list entry of -1
-// selects zero, whatever its load of row 0 returned.)  With allow_route the
-// GEMM also runs the pooling backward below it where route_into allows, and
-// *routed says whether it did.
+// selects zero, whatever its load of row 0 returned.)  Outside a chain of stages
+// (chained = false) a 1x1 layer's GEMM covers row 0 too, its own window.  In a
+// chain the GEMM also runs the pooling backward below it where route_into allows
+// (*routed), or sums the bias gradient of a 1x1 layer below (*summed).
 static hipError_t rows_below(sscn_net* net, int s, hipStream_t st, const ExtraTask* extra = nullptr,
-                             bool allow_route = false, bool* routed = nullptr) {
+                             bool chained = false, bool* routed = nullptr, bool* summed = nullptr) {
   if (routed) *routed = false;
+  if (summed) *summed = false;
   const LayerPlan& L = net->L[s];
   const LayerPlan& Lb = net->L[s - 1];
   if (L.kind == 2) {
@@ -974,13 +992,20 @@ static hipError_t rows_below(sscn_net* net, int s, hipStream_t st, const ExtraTa
   g.rows_dev = net->counts + s - 1;
   g.rows_add = 1;
   g.row_begin = 1;
-  if (L.A == 1) {  // 1x1 layer: row i below takes row i's gradient, ground row included
+  if (L.A == 1) {  // 1x1 layer: row i below takes row i's gradient
     g.rmap = nullptr;
-    g.row_begin = 0;
+    if (!chained) g.row_begin = 0;
   }
   set_plan(net, g, P.pd, P.rows_d, net->gpart);
+  const DropArgs dr = conv_drop(net, s);
   int rac = 0, rbm = 0, rtiles = 0;
-  if (allow_route && route_into(net, s, &rac, &rbm, &rtiles)) {
+  if (chained && summed && !dr.on && (rtiles = (int)sum_tiles(net, s, &rbm)) > 0) {
+    g.sums = 1;
+    g.pr = ground_args(net, s - 1, false);
+    g.pr.PM = rtiles;  // one partial per row tile
+    *summed = true;
+  }
+  if (chained && route_into(net, s, &rac, &rbm, &rtiles)) {
     g.route = 1;
     g.route_ac = rac;
     g.pr = ground_args(net, s - 2, true);
@@ -988,7 +1013,6 @@ static hipError_t rows_below(sscn_net* net, int s, hipStream_t st, const ExtraTa
     if (routed) *routed = true;
   }
   hipError_t e = timed_gemm(net, g, Lb.cap + 1, st, s, SSCN_ROLE_INPUT_GRAD);
-  const DropArgs dr = conv_drop(net, s);
   if (e == hipSuccess && dr.on)  // through the dropout of this convolution's input: rows >= 1, in place
     e = timed(net, SSCN_KC_DROPOUT, st, [&] {
       return launch_dropout_rows(net->bf16, Lb.grad, Lb.grad, Lb.Cp, net->counts + s - 1, Lb.cap + 1, dr, st);
@@ -1143,21 +1167,21 @@ sscn_status sscn_backward(sscn_net* net, float* const* h_dW, float* const* h_db,
   hb.PM = net->pool_parts;
   // Stages from the top down, all on the caller's stream.  Per convolution:
   // its bias and ground-row sums (with a pooling layer above they come out of
-  // that layer's backward), rows >= 1 of the gradient below, the final ground
-  // pass (row 0 of delta, db, D0) and row 0 of the gradient below.  The final
-  // pass needs only the sums and rides as extra workgroups on the input-gradient
-  // GEMM, which reads delta rows >= 1 only (a 1x1 layer's GEMM reads row 0 too:
-  // it rides there only when the pass does not rewrite row 0); row 0 below needs
-  // D0 and rides on the next launch.
+  // that layer's backward, for a 1x1 layer out of the GEMM that writes its delta),
+  // rows >= 1 of the gradient below, the final ground pass (row 0 of delta, db, D0)
+  // and row 0 of the gradient below.  The final pass needs only the sums and rides
+  // as extra workgroups on the input-gradient GEMM, which reads delta rows >= 1
+  // only; row 0 below needs D0 and rides on the next launch.
   //
   // A pooling layer's backward runs in the epilogue of the GEMM that computes
   // its gradient where route_into allows: its row 0 (row 0 below the
   // convolution above) then cannot ride on the next launch, whose final pass
-  // reads it, and is computed by that final pass itself (extra task kind 3).
+  // reads it, and is computed by that final pass itself (extra task kind 3); so is
+  // row 0 of a 1x1 layer's delta where no launch stands between.
   ExtraTask pending{};  // row 0 of a gradient below, waiting for the next launch
   ExtraTask pool_row0{};  // row 0 of a routed pooling layer's gradient, for the final pass below it
   ExtraTask deferred_fin{};  // the first layer's final pass, when no launch of the stage loop follows it
-  bool routed[MAX_LAYERS] = {};
+  bool routed[MAX_LAYERS] = {}, summed[MAX_LAYERS] = {};
   for (int s = top; s >= 1; --s) {
     const LayerPlan& L = net->L[s];
     hipError_t e = hipSuccess;
@@ -1172,7 +1196,7 @@ sscn_status sscn_backward(sscn_net* net, float* const* h_dW, float* const* h_db,
       pending = ExtraTask{};
     } else {
       const bool pool_above = s < top && net->L[s + 1].kind == 2;
-      const bool row0 = needs_row0(net, s) && L.A > 1;
+      const bool row0 = needs_row0(net, s);
       ExtraTask fin = final_task(net, s, pool_above);
       if (pool_above && routed[s + 1]) {  // partials from the routed GEMM above, its row 0 computed here
         int rac = 0, rbm = 0, rtiles = 0;
@@ -1189,6 +1213,15 @@ sscn_status sscn_backward(sscn_net* net, float* const* h_dW, float* const* h_db,
         fin.g.Y_below = L.X;
         if (pending.kind) return SSCN_ERR_HIP;  // nothing precedes the top layer
         e = timed(net, SSCN_KC_HEAD, st, [&] { return launch_head_backward(net->bf16, hb, fin.AC, st); });
+      } else if (summed[s]) {  // partials from the GEMM above, this layer's row 0 computed here
+        int bm = 0;
+        fin.g.B2 = fin.g.PM = (int)sum_tiles(net, s + 1, &bm);
+        fin.g.route_bm = bm;
+        fin.g.n_pool = net->counts + s;
+        if (pending.kind != 2) return SSCN_ERR_HIP;
+        fin.kind = 3;
+        fin.r = pending.r;
+        pending = ExtraTask{};
       } else if (!pool_above) {  // the sums over delta rows, as their own launch
         const GroundArgs g = ground_args(net, s, false);
         e = timed(net, SSCN_KC_GROUND, st, [&] {
@@ -1197,29 +1230,13 @@ sscn_status sscn_backward(sscn_net* net, float* const* h_dW, float* const* h_db,
         pending = ExtraTask{};
       }
       const bool gemm_below = s > 1 || net->want_dfeats;
-      // the final pass writes row 0 of delta when it finishes a pooling layer's (or
-      // the head's) sums: then only a GEMM that does not read row 0 may carry it
-      const bool writes_row0 = pool_above || s == top;
-      if (e == hipSuccess && gemm_below && (L.A > 1 || !writes_row0)) {
-        e = rows_below(net, s, st, &fin, true, s >= 2 ? &routed[s - 1] : nullptr);
-      } else if (e == hipSuccess && !gemm_below && s == 1) {
+      if (e == hipSuccess && gemm_below) {
+        e = rows_below(net, s, st, &fin, true, s >= 2 ? &routed[s - 1] : nullptr, s >= 2 ? &summed[s - 1] : nullptr);
+      } else if (e == hipSuccess) {
         // the first layer's final pass: on the weight-gradient launches at the end
         if (pending.kind) e = timed(net, SSCN_KC_GROUND, st, [&] { return launch_extra(net->bf16, pending, st); });
         pending = ExtraTask{};
         deferred_fin = fin;
-      } else if (e == hipSuccess) {
-        if (fin.kind == 3) {  // the final pass with its row 0 above, as a launch of its own
-          if (pending.kind)
-            e = timed(net, SSCN_KC_GROUND, st, [&] { return launch_extra(net->bf16, pending, st); });
-          if (e == hipSuccess) e = timed(net, SSCN_KC_GROUND, st, [&] { return launch_extra(net->bf16, fin, st); });
-        } else {
-          const GroundArgs g = fin.g;
-          e = timed(net, SSCN_KC_GROUND, st, [&] {
-            return launch_ground(net->bf16, g, fin.AC, 2, st, pending.kind ? &pending : nullptr);
-          });
-        }
-        pending = ExtraTask{};
-        if (e == hipSuccess && gemm_below) e = rows_below(net, s, st, nullptr, true, s >= 2 ? &routed[s - 1] : nullptr);
       }
       if (row0) pending = row0_task(net, s);
     }

@@ -249,10 +249,11 @@ struct StagedRoute {
 template <typename T, class C, int CS, int AC, int LDSF>
 __device__ inline void store_staged(const GemmArgs& a, const T* Cs, int m0, int n0, int tm, int rows, float* lds) {
   constexpr int VE = C::VE, BM = C::BM, BN = C::BN, NT = C::NT, NV = BN / VE;
+  constexpr bool SUMS = AC == MASK_MODE;  // the column sums of the rows stored (GemmArgs::sums)
   constexpr int J = AC >= 0 ? 2 + AC : 1;
   static_assert(NT % NV == 0, "each thread keeps one channel vector");
   float acc[J][VE];
-  if constexpr (AC >= 0) {
+  if constexpr (AC >= 0 || SUMS) {
 #pragma unroll
     for (int k = 0; k < J; ++k)
 #pragma unroll
@@ -284,9 +285,15 @@ __device__ inline void store_staged(const GemmArgs& a, const T* Cs, int m0, int 
         *(u32x4*)((T*)a.out + (int64_t)m * a.out_stride + n) = o;
         if constexpr (AC >= 0)
           if (m >= 1) pool_route_item<T, AC>(a.pr, m, n, (const T*)&o, acc);
+        if constexpr (SUMS) {
+#pragma unroll
+          for (int e = 0; e < VE; ++e) acc[0][e] += Elem<T>::to_f32(((const T*)&o)[e]);
+        }
       }
     }
   }
+  if constexpr (SUMS)
+    if (a.sums) tile_slot_sums<VE, J, NT, NV, LDSF>(acc, lds, a.pr, n0, tm, 1);
   if constexpr (AC >= 0) tile_slot_sums<VE, J, NT, NV, LDSF>(acc, lds, a.pr, n0, tm);
 }
 
@@ -368,7 +375,11 @@ __global__ void __launch_bounds__(C::NT) k_gemm_gather(GemmArgs a) {
   constexpr int NST = (BM + BN >= 256 || (sizeof(T) == 2 && (RAC >= 0 || POOL))) ? 2 : 3;
   constexpr int STG = (BM + BN) * BK;          // elements per stage
   constexpr int LPS = C::AV + C::BV;           // loads per thread and slab
-  constexpr int SMEM = NST * STG > BM * CS ? NST * STG : BM * CS;
+  constexpr bool MASK = RAC == MASK_MODE;
+  // the masked store stages the layer below's tile beside its own, where that leaves two workgroups a compute unit
+  constexpr bool MASK_LDS = MASK && BM * (CS + BN) * (int)sizeof(T) <= 80 * 1024;
+  constexpr int OUT = BM * CS + (MASK_LDS ? BM * BN : 0);
+  constexpr int SMEM = NST * STG > OUT ? NST * STG : OUT;
   __shared__ __attribute__((aligned(16))) T smem[SMEM];
   // sized at launch: [BM * A] window entries (bf16: the source row's byte offset,
   // GATHER_NONE where there is none; float32: its row, -1), then (bf16, A > 1) one
@@ -456,6 +467,21 @@ __global__ void __launch_bounds__(C::NT) k_gemm_gather(GemmArgs a) {
 #pragma unroll
       for (int j = 0; j < C::TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+    // The masked store's output tile of the layer below: 16-byte loads before the K
+    // loop, through LDS after it.  (Loaded where they are used, two bytes a lane in
+    // the MFMA result's layout: 29.4 us for the 128 x 128 tiles of DeepCNiN(5,50)'s
+    // second input gradient, 19.4 like this.)
+    constexpr int MV = MASK_LDS ? BM * BN / VE / NT : 1;
+    u32x4 mk[MV];
+    if constexpr (MASK_LDS) {
+      static_assert(MV * NT * VE == BM * BN, "whole vectors per thread");
+#pragma unroll
+      for (int i = 0; i < MV; ++i) {
+        const int v = tid + i * NT, r = v / (BN / VE), n = n0 + (v - r * (BN / VE)) * VE;
+        const bool in = m0 + r < rows && n < a.out_cols;
+        mk[i] = *(const u32x4*)((const T*)a.mask + (in ? (int64_t)(m0 + r) * a.mask_stride + n : 0));
+      }
+    }
     // this wave's column blocks below the result's width
     const int live =
         __builtin_amdgcn_readfirstlane((min(a.out_cols - n0, BN) - wn * 16 + 16 * C::WN - 1) / (16 * C::WN));
@@ -565,6 +591,12 @@ __global__ void __launch_bounds__(C::NT) k_gemm_gather(GemmArgs a) {
         }
     } else if (epi_stores_T(a.epi)) {
       T* Cs = smem;
+      T* Ms = smem + BM * CS;
+      if constexpr (MASK_LDS) {
+#pragma unroll
+        for (int i = 0; i < MV; ++i) *(u32x4*)(Ms + (tid + i * NT) * VE) = mk[i];
+        __syncthreads();
+      }
 #pragma unroll
       for (int i = 0; i < C::TM; ++i)
 #pragma unroll
@@ -574,11 +606,14 @@ __global__ void __launch_bounds__(C::NT) k_gemm_gather(GemmArgs a) {
           for (int r = 0; r < 4; ++r) {
             const int ml = wm * C::TM * 16 + i * 16 + g * 4 + r;
             // the gradients' epilogues (EPI_STORE, EPI_STORE_MASK) have no bias or rectifier
-            float v = RAC >= 0 || RAC == MASK_MODE ? acc[i][j][r] : epi_value<T>(a, acc[i][j][r], bias[j]);
-            if constexpr (RAC == MASK_MODE)  // the rectifier derivative of the layer below,
-              if (m0 + ml < rows && n0 + nl < a.out_cols)  // before the one rounding to storage
+            float v = RAC >= 0 || MASK ? acc[i][j][r] : epi_value<T>(a, acc[i][j][r], bias[j]);
+            if constexpr (MASK) {  // the rectifier derivative of the layer below, before the one rounding to storage
+              if constexpr (MASK_LDS)
+                v *= act_factor(Elem<T>::to_f32(Ms[ml * BN + nl]), a.slope);
+              else if (m0 + ml < rows && n0 + nl < a.out_cols)
                 v *= act_factor(
                     Elem<T>::to_f32(((const T*)a.mask)[(int64_t)(m0 + ml) * a.mask_stride + n0 + nl]), a.slope);
+            }
             Cs[ml * CS + nl] = Elem<T>::from_f32(v);
           }
         }
@@ -1132,6 +1167,9 @@ hipError_t launch_gemm(bool bf16, const GemmArgs& args, int64_t max_rows, hipStr
                      (a.epi != EPI_BIAS_RELU && a.epi != EPI_BIAS_LRELU)))
     return hipErrorInvalidValue;
   if (a.epi == EPI_STORE_MASK && a.bias) return hipErrorInvalidValue;
+  if (a.sums && (a.epi != EPI_STORE_MASK || a.ksplit != 1 || a.row_begin != 1 || !a.pr.part || a.pr.cp != a.out_cols ||
+                 (max_rows - a.row_begin + gemm_bm(bf16, a.cfg) - 1) / gemm_bm(bf16, a.cfg) > a.pr.PM))
+    return hipErrorInvalidValue;
   if (a.route) {  // pooling backward in the epilogue: one partial per row tile
     const int bm = gemm_bm(bf16, a.cfg);
     if (a.epi != EPI_STORE || a.bias || a.ksplit != 1 || (a.route_ac != 0 && a.route_ac != 4) ||

@@ -65,10 +65,11 @@ __device__ inline void store_vectors(const GemmArgs& a, float (*red)[DIRECT_BM][
                                      const PrefetchT<T, AC, PRE>& pre) {
   constexpr int VE = Elem<T>::VE;
   constexpr int BM = DIRECT_BM, BN = DIRECT_BN, NT = 64 * SK, NV = BN / VE;
+  constexpr bool SUMS = AC == MASK_MODE;  // the column sums of the rows stored (GemmArgs::sums)
   constexpr int J = AC >= 0 ? 2 + AC : 1;
   static_assert(NT % NV == 0, "each thread keeps one column group");
   float acc[J][VE];
-  if constexpr (AC >= 0) {
+  if constexpr (AC >= 0 || SUMS) {
 #pragma unroll
     for (int k = 0; k < J; ++k)
 #pragma unroll
@@ -90,6 +91,10 @@ __device__ inline void store_vectors(const GemmArgs& a, float (*red)[DIRECT_BM][
       ((T*)&o)[e] = Elem<T>::from_f32(x);
     }
     *(v4u*)((T*)a.out + (int64_t)m * a.out_stride + n) = o;
+    if constexpr (SUMS) {
+#pragma unroll
+      for (int e = 0; e < VE; ++e) acc[0][e] += Elem<T>::to_f32(((const T*)&o)[e]);
+    }
     if constexpr (AC >= 0) {
       if (m >= 1) {
         if constexpr (PRE)  // this thread's only row, its loads issued earlier
@@ -100,6 +105,8 @@ __device__ inline void store_vectors(const GemmArgs& a, float (*red)[DIRECT_BM][
     }
   }
   if constexpr (AC >= 0) tile_slot_sums<VE, J, NT, NV, LDSF>(acc, &red[0][0][0], a.pr, n0, tm);
+  if constexpr (SUMS)
+    if (a.sums) tile_slot_sums<VE, J, NT, NV, LDSF>(acc, &red[0][0][0], a.pr, n0, tm, 1);
 }
 
 // Pooling forward in the epilogue (GemmArgs::pool_fwd): the tile's rows are
@@ -342,6 +349,7 @@ static void launch_direct_sk(const GemmArgs& a, int64_t max_rows, hipStream_t st
   const int64_t tiles = ((span + DIRECT_BM - 1) / DIRECT_BM) * (a.Npad / DIRECT_BN);
   const int grid = (int)std::min<int64_t>(std::max<int64_t>(tiles, 1), 2048) + (a.x.kind ? a.x.blocks : 0);
   void (*kern)(GemmArgs) = a.pool_fwd ? k_gemm_direct<T, SK, POOL_FWD_MODE>
+                           : a.epi == EPI_STORE_MASK ? k_gemm_direct<T, SK, MASK_MODE>
                            : !a.route ? k_gemm_direct<T, SK, -1>
                            : a.route_ac == 4 ? k_gemm_direct<T, SK, 4>
                                              : k_gemm_direct<T, SK, 0>;

@@ -16,7 +16,7 @@ namespace sscn {
 //   with a pooling layer above, row 0 of delta is
 //     z0 = f'(Y_below[0][c]) * (dY[0][c] + slot 0), written to delta[0][c]
 //     (dY[0][c] read, or passed in as dy0 when inline_dy0);
-//   without one, z0 = delta[0][c] as stored;
+//   without one, z0 = delta[0][c] as stored (read, or passed in as dy0);
 //   db[c] = slot 1 + z0,  D0[f][c] = slot 2+f + z0  (row 0 reads the ground row
 //   at every window position), for c < c_out.
 template <typename T, int AC>
@@ -67,10 +67,11 @@ __device__ inline void ground_final_block(const GroundArgs& g, int c, bool inlin
     dZ[c] = g0;
     z0 = Elem<T>::to_f32(g0);
   } else {
-    z0 = Elem<T>::to_f32(dZ[c]);
+    z0 = inline_dy0 ? dy0 : Elem<T>::to_f32(dZ[c]);
   }
   if (c >= g.c_out) return;
   g.db[c] = tot[1] + z0;
+  if (g.d0_row) g.D0[c] = z0;
 #pragma unroll
   for (int k = 0; k < AC; ++k) g.D0[(int64_t)k * g.c_out + c] = tot[2 + k] + z0;
 }

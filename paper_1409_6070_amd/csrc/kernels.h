@@ -77,10 +77,13 @@ struct GroundArgs {
   int32_t PM;   // partial stride, >= B1, B2
   float* db;
   float* D0;
-  // > 0: the partials come from the epilogue of the GEMM that wrote dY, one per
-  // tile of route_bm pooling rows (rows 1..n_pool): only the first
-  // ceil(n_pool / route_bm) of the B1 = B2 are read
+  // > 0: the partials come from the epilogue of the GEMM that wrote dY (or, with no
+  // pooling layer above, dZ), one per tile of route_bm rows (rows 1..n_pool): only
+  // the first ceil(n_pool / route_bm) of the B1 and B2 are read
   int32_t route_bm;
+  // a window of one (AC = 0): D0 [c_out] is delta row 0 itself, the only row that
+  // reads the ground row
+  int32_t d0_row;
 };
 
 // Row 0 of the gradient below a convolution (its ground row): for input channel
@@ -100,8 +103,9 @@ struct Row0Args {
 // last `blocks` workgroups of the grid), independent of that launch's own work:
 //   kind 1: the ground final pass of a convolution (one workgroup per channel, cp);
 //   kind 2: row 0 of the gradient below a convolution (one per channel, cp_in);
-//   kind 3: kind 1 below a pooling layer whose row 0 gradient (kind 2 of the
-//           convolution above it, r) is computed first, in the same workgroup.
+//   kind 3: kind 1 whose row 0 (kind 2 of the convolution above, r) is computed
+//           first, in the same workgroup: row 0 of the pooling layer's gradient or,
+//           below a convolution, of this one's own delta.
 struct ExtraTask {
   int32_t kind;    // 0: none
   int32_t blocks;
@@ -154,7 +158,11 @@ struct GemmArgs {
   // partial sums, one partial per row tile; pr describes both layers (its dY
   // field is unused) and route_ac is the convolution's finished window count
   // (0 or 4).
+  // EPI_STORE_MASK with sums = 1 (ksplit == 1, row_begin == 1): the stored rows are
+  // a convolution's delta, whose column sums over each row tile go to slot 1 of pr's
+  // partials (the bias gradient).
   int32_t route;
+  int32_t sums;
   int32_t route_ac;
   GroundArgs pr;
   // Pooling forward in the epilogue (pool_fwd = 1; a convolution with the

@@ -185,11 +185,12 @@ __device__ inline void pool_route_item(const GroundArgs& g, int64_t o, int c, co
 // t % NV of the tile (NV vectors of VE channels from n0) over its rows.  Up to
 // LDSF / (NT * VE) slots at a time go through lds (LDSF floats); each
 // (slot, channel) is then summed by one thread over the NT / NV threads of its
-// vector in thread order, and part[(k * cp + c) * PM + tm] receives slot k of
-// channel c < cp.  All threads of the block call it; it synchronises before
+// vector in thread order, and part[((slot0 + k) * cp + c) * PM + tm] receives slot
+// k of channel c < cp.  All threads of the block call it; it synchronises before
 // its first use of lds, and the caller before reusing lds.
 template <int VE, int J, int NT, int NV, int LDSF>
-__device__ inline void tile_slot_sums(const float (&acc)[J][VE], float* lds, const GroundArgs& g, int n0, int tm) {
+__device__ inline void tile_slot_sums(const float (&acc)[J][VE], float* lds, const GroundArgs& g, int n0, int tm,
+                                      int slot0 = 0) {
   typedef float f4 __attribute__((ext_vector_type(4)));
   constexpr int RL = NT / NV;  // threads per channel vector
   constexpr int SBF = LDSF / (NT * VE);
@@ -215,7 +216,7 @@ __device__ inline void tile_slot_sums(const float (&acc)[J][VE], float* lds, con
 #pragma unroll 8
       for (int l = 0; l < RL; ++l) s += col[l * NV * VE];
       const int c = n0 + e;
-      if (c < g.cp) g.part[((int64_t)(k0 + kk) * g.cp + c) * g.PM + tm] = s;
+      if (c < g.cp) g.part[((int64_t)(slot0 + k0 + kk) * g.cp + c) * g.PM + tm] = s;
     }
   }
 }
