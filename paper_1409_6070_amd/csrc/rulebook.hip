@@ -18,7 +18,7 @@
 // the windows below is contiguous).  Every layer's bitmap therefore comes
 // straight from the input bitmap, one wave per (sample, layer), with no chain
 // through the layers: the rows of each square are ORed word-parallel, then
-// each output bit tests its column range.  The rows, window lists and
+// dilated to the square's width and thinned to every a-th column.  The rows, window lists and
 // transposes of a layer then come from one pass over its bitmap words: a
 // workgroup lists its words' sites in row order in LDS and its threads take
 // them one after another.  The sample offsets (exclusive scan of the
@@ -31,6 +31,7 @@
 // inserts into one that is all zero and clears the other for the next build,
 // so no clearing launch precedes the insertion.
 
+#include "bit_rows.h"
 #include "common.h"
 #include "kernels.h"
 
@@ -158,47 +159,13 @@ __device__ inline int insert_sample(const int32_t* coords, int beg, int end, int
   return err;
 }
 
-// Bits 0, 2, 4, .. of v, packed into 32 bits.
-__device__ inline uint64_t even_bits(uint64_t v) {
-  v &= 0x5555555555555555ull;
-  v = (v | (v >> 1)) & 0x3333333333333333ull;
-  v = (v | (v >> 2)) & 0x0f0f0f0f0f0f0f0full;
-  v = (v | (v >> 4)) & 0x00ff00ff00ff00ffull;
-  v = (v | (v >> 8)) & 0x0000ffff0000ffffull;
-  return (v | (v >> 16)) & 0xffffffffull;
-}
-
-// One output row from the OR of its input rows, in place: row (nw words, the
-// bits past the grid zero) becomes bit X = any of bits [a X, a X + r), a a power
-// of two.  The dilation doubles its reach (log2 r shifts of the whole row), then
-// every a-th bit is kept (log2 a rounds of packing the even bits): a few dozen
-// operations a word where testing each output bit's range took its whole row
-// of tests (layers of a 192 x 192 grid, three words a row: 26.4 -> 12.9 us for
-// the launch at batch 64).
-__device__ inline void dilate_row(uint64_t* row, int nw, int a, int r) {
-  for (int len = 1; len < r;) {
-    const int sh = min(len, r - len), ws = sh >> 6, bs = sh & 63;
-    for (int w = 0; w < nw; ++w) {  // words >= w only: in place
-      const uint64_t lo = w + ws < nw ? row[w + ws] : 0ull, hi = w + ws + 1 < nw ? row[w + ws + 1] : 0ull;
-      row[w] |= bs ? (lo >> bs) | (hi << (64 - bs)) : lo;
-    }
-    len += sh;
-  }
-  for (int st = a; st > 1; st >>= 1) {
-    for (int w = 0; w < (nw + 1) / 2; ++w) {
-      const uint64_t lo = row[2 * w], hi = 2 * w + 1 < nw ? row[2 * w + 1] : 0ull;
-      row[w] = even_bits(lo) | (even_bits(hi) << 32);
-    }
-    nw = (nw + 1) / 2;
-  }
-}
-
 // Layer s of sample b, b = blockIdx / nlayers, s = blockIdx % nlayers (one
 // wave): the sample's input bitmap goes to LDS (read from the inserted bitmap,
 // or, with the sites grouped by sample, built here from the sample's own
 // sites by LDS atomic ORs, the input layer's wave storing it); each lane takes whole output
-// rows, ORs the input rows of their squares into its own row buffer, and
-// dilates and thins that row word-parallel (dilate_row).  Then the layer's word prefix and count, as
+// rows, ORs the input rows of their squares, and dilates and thins that row
+// word-parallel: in registers for grids of up to 192 columns (dilate_words), in its
+// own row buffer above (dilate_row).  Then the layer's word prefix and count, as
 // the layer-by-layer definition gives them.  Every workgroup also clears its
 // share of the next build's input bitmap; workgroups of samples b >= batch only
 // clear.
@@ -270,7 +237,7 @@ __global__ void __launch_bounds__(64) k_rb_bitmaps(RulebookArgs a, int32_t max_w
     const int Y = Y0 + t / P, sub = t % P;
     const bool live = Y < So;
     const int y_end = live ? min(ra * Y + rr, S0) : 0;
-    for (int w = 0; w < W0; ++w) {  // OR of the square's input rows
+    auto or_rows = [&](int w) {  // word w of the OR of the square's input rows
       uint64_t v = 0;
 #pragma unroll 4
       for (int y = ra * Y + sub; y < y_end; y += P) v |= in[y * W0 + w];
@@ -278,11 +245,31 @@ __global__ void __launch_bounds__(64) k_rb_bitmaps(RulebookArgs a, int32_t max_w
         const uint32_t lo = __shfl_xor((uint32_t)v, m, 64), hi = __shfl_xor((uint32_t)(v >> 32), m, 64);
         v |= ((uint64_t)hi << 32) | lo;
       }
-      row[w] = v;
+      return v;
+    };
+    auto in_registers = [&](auto nw_c) {
+      constexpr int NW = decltype(nw_c)::value;
+      uint64_t v[NW];
+#pragma unroll
+      for (int w = 0; w < NW; ++w) v[w] = or_rows(w);
+      if (!live || sub) return;
+      dilate_words(v, ra, rr);
+#pragma unroll
+      for (int w = 0; w < NW; ++w)
+        if (w < Wo) out[Y * Wo + w] = v[w] & row_mask_word(w, So);
+    };
+    if (W0 == 1) {
+      in_registers(std::integral_constant<int, 1>{});
+    } else if (W0 == 2) {
+      in_registers(std::integral_constant<int, 2>{});
+    } else if (W0 == 3) {
+      in_registers(std::integral_constant<int, 3>{});
+    } else {
+      for (int w = 0; w < W0; ++w) row[w] = or_rows(w);
+      if (!live || sub) continue;
+      dilate_row(row, W0, ra, rr);
+      for (int w = 0; w < Wo; ++w) out[Y * Wo + w] = row[w] & row_mask_word(w, So);
     }
-    if (!live || sub) continue;
-    dilate_row(row, W0, ra, rr);
-    for (int w = 0; w < Wo; ++w) out[Y * Wo + w] = row[w] & row_mask_word(w, So);
   }
   __syncthreads();
   uint64_t* dst = Lo.bits + (int64_t)b * nwo;
