@@ -150,6 +150,40 @@ __global__ void __launch_bounds__(ENC_THREADS) k_enc_prefix(EncodeArgs a) {
   if (t == ENC_THREADS - 1) a.scount[b] = scratch[ENC_THREADS - 1];
 }
 
+// Batches up to this size have their sample offsets summed inside the site kernel,
+// each workgroup taking all counts before its sample; above it that work, which
+// grows with the square of the batch, goes to a launch of its own.  (Whole call, in
+// the site kernel / on its own: 98 / 119 us at 8193 samples of a 24 x 24 grid, 143 /
+// 162 at 16384, 261 / 257 at 32768, 587 / 434 at 65536; 4.83 / 1.19 ms at 262144 of a
+// 12 x 12 one.)
+constexpr int ENC_SUM_MAX = 24576;
+
+// Sample offsets (exclusive scan of the counts) and the total, one workgroup.
+__global__ void __launch_bounds__(ENC_THREADS) k_enc_offsets(EncodeArgs a) {
+  __shared__ int scratch[ENC_THREADS];
+  const int t = threadIdx.x;
+  const int per = (a.batch + ENC_THREADS - 1) / ENC_THREADS;
+  const int beg = min(a.batch, t * per), end = min(a.batch, beg + per);
+  int local = 0;
+#pragma unroll 8
+  for (int i = beg; i < end; ++i) local += a.scount[i];
+  scratch[t] = local;
+  __syncthreads();
+  for (int off = 1; off < ENC_THREADS; off <<= 1) {
+    const int v = t >= off ? scratch[t - off] : 0;
+    __syncthreads();
+    scratch[t] += v;
+    __syncthreads();
+  }
+  int run = scratch[t] - local;
+#pragma unroll 8
+  for (int i = beg; i < end; ++i) {
+    a.soff[i] = run;
+    run += a.scount[i];
+  }
+  if (t == ENC_THREADS - 1) a.total[0] = scratch[ENC_THREADS - 1];
+}
+
 // Row (0-based) of the marked pixel (b, y, x).
 __device__ inline int enc_row(const EncodeArgs& a, int b, int y, int x) {
   const int64_t idx = ((int64_t)b * a.N + y) * a.Wd + (x >> 6);
@@ -158,21 +192,28 @@ __device__ inline int enc_row(const EncodeArgs& a, int b, int y, int x) {
 }
 
 // Sites in ascending (b, y, x) order, the first max_sites of them: workgroup b
-// takes sample b's words, after summing the counts of the samples before it for
-// its offset (the last sample's gives the total).
+// takes sample b's words.  SUM: it first sums the counts of the samples before it
+// for its offset (the last sample's gives the total); otherwise the offsets are
+// stored already.
+template <bool SUM>
 __global__ void __launch_bounds__(ENC_THREADS) k_enc_sites(EncodeArgs a) {
-  __shared__ int part[ENC_THREADS / 64];
   const int b = blockIdx.x, t = threadIdx.x;
-  int sum = 0;
+  int off;
+  if constexpr (SUM) {
+    __shared__ int part[ENC_THREADS / 64];
+    int sum = 0;
 #pragma unroll 4
-  for (int i = t; i < b; i += ENC_THREADS) sum += a.scount[i];
-  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
-  if ((t & 63) == 0) part[t >> 6] = sum;
-  __syncthreads();
-  const int off = (part[0] + part[1]) + (part[2] + part[3]);
-  if (t == 0) {
-    a.soff[b] = off;
-    if (b == a.batch - 1) a.total[0] = off + a.scount[b];
+    for (int i = t; i < b; i += ENC_THREADS) sum += a.scount[i];
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    if ((t & 63) == 0) part[t >> 6] = sum;
+    __syncthreads();
+    off = (part[0] + part[1]) + (part[2] + part[3]);
+    if (t == 0) {
+      a.soff[b] = off;
+      if (b == a.batch - 1) a.total[0] = off + a.scount[b];
+    }
+  } else {
+    off = a.soff[b];
   }
   const int nw = a.N * a.Wd;
   for (int rem = t; rem < nw; rem += ENC_THREADS) {
@@ -233,15 +274,21 @@ __global__ void __launch_bounds__(256) k_enc_feats(EncodeArgs a, T* feats) {
 
 static int enc_grid(int64_t items) { return (int)std::max<int64_t>(1, std::min<int64_t>((items + 255) / 256, 4096)); }
 
-// Six launches (ten with the clears, the check and the offsets as their own: 33 us
-// of kernels for 100 pen paths, 22 like this), each a few dependent loads long.
+// Six launches, seven above ENC_SUM_MAX samples (ten with the clears, the check and
+// the offsets as their own: 33 us of kernels for 100 pen paths, 22 like this), each a
+// few dependent loads long.
 hipError_t launch_encode(bool bf16, const EncodeArgs& a, void* feats, hipStream_t st) {
   const int64_t words = (int64_t)a.batch * a.N * a.Wd;
   hipLaunchKernelGGL(k_enc_clear, dim3(enc_grid(std::max(words / 2, (int64_t)a.max_sites * 2))), dim3(256), 0, st, a);
   hipLaunchKernelGGL(k_enc_mark, dim3(enc_grid(std::max(a.n_points, a.n_strokes + 1))), dim3(256), 0, st, a);
   if (a.batch > 0) {
     hipLaunchKernelGGL(k_enc_prefix, dim3(a.batch), dim3(ENC_THREADS), 0, st, a);
-    hipLaunchKernelGGL(k_enc_sites, dim3(a.batch), dim3(ENC_THREADS), 0, st, a);
+    if (a.batch <= ENC_SUM_MAX) {
+      hipLaunchKernelGGL(k_enc_sites<true>, dim3(a.batch), dim3(ENC_THREADS), 0, st, a);
+    } else {
+      hipLaunchKernelGGL(k_enc_offsets, dim3(1), dim3(ENC_THREADS), 0, st, a);
+      hipLaunchKernelGGL(k_enc_sites<false>, dim3(a.batch), dim3(ENC_THREADS), 0, st, a);
+    }
   }
   if (a.n_points > 0 && a.n_strokes > 0 && a.batch > 0)
     hipLaunchKernelGGL(k_enc_moves, dim3(enc_grid(a.n_points)), dim3(256), 0, st, a);
