@@ -18,6 +18,7 @@
 
 #include "common.h"
 #include "epilogue.h"
+#include "gemm_rules.h"
 #include "pool_route.h"
 #include "ground_tasks.h"
 #include "kernels.h"
@@ -407,18 +408,8 @@ __global__ void __launch_bounds__(C::NT) k_gemm_gather(GemmArgs a) {
   bool tabled = false;
 
   const int grid = own_grid(a.x);
-  // Several column tiles to a gathered row tile: consecutive workgroups, which the
-  // hardware deals round-robin to the eight XCDs, take tiles ntiles / 8 apart, so
-  // that a row tile's column tiles and its neighbours read their rows through one
-  // L2.  (DeepCNet(5,50) at batch 1600: 145.6 -> 137.1 us for the third forward,
-  // 225.2 -> 217.9 for the third input gradient; at batch 100 13.9 -> 13.2 and 19.2
-  // -> 18.9.  One column tile, or the softmax layer's few rows, lose by it: 16.2 ->
-  // 16.9, 29.3 -> 48.9.)
-  const bool by_xcd = tiles_n > 1 && a.rmap && a.A > 1 && a.ksplit == 1;
-  const int xcd = by_xcd ? (int)blockIdx.x & 7 : 0, nx = by_xcd ? 8 : 1;
-  const int per_x = (ntiles + nx - 1) / nx;
-  const int tile_end = min(ntiles, (xcd + 1) * per_x), tile_step = (grid + nx - 1 - xcd) / nx;
-  for (int tile = xcd * per_x + (by_xcd ? (int)blockIdx.x >> 3 : (int)blockIdx.x); tile < tile_end; tile += tile_step) {
+  const TileDeal deal = deal_tiles(ntiles, grid, blockIdx.x, deal_by_xcd(tiles_n, a.rmap != nullptr, a.A, a.ksplit));
+  for (int tile = deal.first; tile < deal.end; tile += deal.step) {
     const int tn = tile % tiles_n;
     const int t2 = tile / tiles_n;
     const int tm = t2 % tiles_m;
@@ -1118,7 +1109,7 @@ template <typename T, class C>
 static void launch_cfg(const GemmArgs& a, int64_t max_rows, hipStream_t st) {
   const int64_t span = max_rows - a.row_begin;
   const int64_t tiles = ((span + C::BM - 1) / C::BM) * (a.Npad / C::BN) * a.ksplit;
-  const int grid = (int)std::min<int64_t>(std::max<int64_t>(tiles, 1), device_grid_limit()) +
+  const int grid = deal_grid(tiles, device_grid_limit(), deal_by_xcd(a.Npad / C::BN, a.rmap != nullptr, a.A, a.ksplit)) +
                    (a.x.kind ? a.x.blocks : 0);
   const bool timed = a.t_start || a.t_stop;
   // the pooling-backward epilogue and the masked store have instantiations of

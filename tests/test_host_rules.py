@@ -14,7 +14,9 @@ def run_host(tmp_path, text):
     src.write_text(text)
     subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-Wno-unknown-pragmas", "-I",
                     os.path.join(ROOT, "paper_1409_6070_amd", "csrc"), str(src), "-o", str(exe)], check=True, timeout=120)
-    return subprocess.run([str(exe)], check=True, timeout=120, stdout=subprocess.PIPE, text=True).stdout
+    r = subprocess.run([str(exe)], timeout=120, stdout=subprocess.PIPE, text=True)
+    assert r.returncode == 0, r.stdout
+    return r.stdout
 
 
 BIT_ROWS = r"""
@@ -67,3 +69,43 @@ int main() {
 def test_bitmap_rows_dilate_and_thin(tmp_path):
     """Grid sides up to 768 (three words a row in registers up to 192), every power-of-two step, every reach."""
     assert int(run_host(tmp_path, BIT_ROWS)) > 100000
+
+
+TILE_DEAL = r"""
+#include "gemm_rules.h"
+#include <cstdio>
+#include <vector>
+using namespace sscn;
+int main() {
+  const int limit = 2048;
+  long n = 0;
+  for (int cap = 1; cap <= 9000; cap = cap < 2200 ? cap + 1 : cap + 37)          // tiles at the row bound
+    for (int nt = cap; nt >= 0; nt = cap < 400 ? nt - 1 : nt - 1 - (cap - nt) / 3)  // tiles of the rows present
+      for (int by = 0; by < 2; ++by) {
+        const int grid = deal_grid(cap, limit, by), plain = deal_grid(cap, limit, false);
+        std::vector<char> seen(nt, 0);
+        int most = 0;
+        for (int b = 0; b < grid; ++b) {
+          const TileDeal d = deal_tiles(nt, grid, b, by);
+          if (d.step < 1) { printf("cap %d tiles %d dealt %d block %d: step %d\n", cap, nt, by, b, d.step); return 1; }
+          int k = 0;
+          for (int t = d.first; t < d.end; t += d.step, ++k)
+            if (t < 0 || t >= nt || seen[t]++) { printf("cap %d tiles %d dealt %d block %d: tile %d\n", cap, nt, by, b, t); return 1; }
+          most = k > most ? k : most;
+        }
+        for (int t = 0; t < nt; ++t)
+          if (!seen[t]) { printf("cap %d tiles %d dealt %d: tile %d left out\n", cap, nt, by, t); return 1; }
+        if (most > (nt + plain - 1) / plain) {
+          printf("cap %d tiles %d dealt %d: %d tiles to a workgroup, %d in plain order\n", cap, nt, by, most, (nt + plain - 1) / plain);
+          return 1;
+        }
+        ++n;
+      }
+  printf("%ld\n", n);
+}
+"""
+
+
+def test_tiles_are_dealt_once_and_evenly(tmp_path):
+    """Every tile once; no workgroup takes more tiles than with one tile after another in plain order."""
+    assert int(run_host(tmp_path, TILE_DEAL)) > 100000
