@@ -18,7 +18,6 @@
 
 #include "common.h"
 #include "epilogue.h"
-#include "gemm_rules.h"
 #include "pool_route.h"
 #include "ground_tasks.h"
 #include "kernels.h"
@@ -1115,11 +1114,12 @@ static void launch_cfg(const GemmArgs& a, int64_t max_rows, hipStream_t st) {
   // the pooling-backward epilogue and the masked store have instantiations of
   // their own (their extra loads and sums would otherwise cost every launch
   // registers)
-  void (*kern)(GemmArgs) = a.pool_fwd ? k_gemm_gather<T, C, POOL_FWD_MODE>
-                           : a.epi == EPI_STORE_MASK ? k_gemm_gather<T, C, MASK_MODE>
-                           : !a.route ? k_gemm_gather<T, C, -1>
-                           : a.route_ac == 4 ? k_gemm_gather<T, C, 4>
-                                             : k_gemm_gather<T, C, 0>;
+  const int mode = gemm_mode(a.pool_fwd, a.epi == EPI_STORE_MASK, a.route, a.route_ac, a.ksplit);
+  void (*kern)(GemmArgs) = mode == POOL_FWD_MODE ? k_gemm_gather<T, C, POOL_FWD_MODE>
+                           : mode == MASK_MODE   ? k_gemm_gather<T, C, MASK_MODE>
+                           : mode == PLAIN_MODE  ? k_gemm_gather<T, C, PLAIN_MODE>
+                           : mode == 4           ? k_gemm_gather<T, C, 4>
+                                                 : k_gemm_gather<T, C, 0>;
   // the window table and the chunk words: a workgroup's LDS follows A and K
   const size_t lds = ((size_t)C::BM * a.A + (sizeof(T) == 2 && a.A > 1 ? a.Kpad / C::VE : 0)) * sizeof(int32_t);
   if (timed)

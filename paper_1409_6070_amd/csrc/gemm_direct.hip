@@ -348,11 +348,12 @@ static void launch_direct_sk(const GemmArgs& a, int64_t max_rows, hipStream_t st
   const int64_t span = max_rows - a.row_begin;
   const int64_t tiles = ((span + DIRECT_BM - 1) / DIRECT_BM) * (a.Npad / DIRECT_BN);
   const int grid = (int)std::min<int64_t>(std::max<int64_t>(tiles, 1), 2048) + (a.x.kind ? a.x.blocks : 0);
-  void (*kern)(GemmArgs) = a.pool_fwd ? k_gemm_direct<T, SK, POOL_FWD_MODE>
-                           : a.epi == EPI_STORE_MASK ? k_gemm_direct<T, SK, MASK_MODE>
-                           : !a.route ? k_gemm_direct<T, SK, -1>
-                           : a.route_ac == 4 ? k_gemm_direct<T, SK, 4>
-                                             : k_gemm_direct<T, SK, 0>;
+  const int mode = gemm_mode(a.pool_fwd, a.epi == EPI_STORE_MASK, a.route, a.route_ac, a.ksplit);
+  void (*kern)(GemmArgs) = mode == POOL_FWD_MODE ? k_gemm_direct<T, SK, POOL_FWD_MODE>
+                           : mode == MASK_MODE   ? k_gemm_direct<T, SK, MASK_MODE>
+                           : mode == PLAIN_MODE  ? k_gemm_direct<T, SK, PLAIN_MODE>
+                           : mode == 4           ? k_gemm_direct<T, SK, 4>
+                                                 : k_gemm_direct<T, SK, 0>;
   if (a.t_start || a.t_stop)
     hipExtLaunchKernelGGL(kern, dim3(grid), dim3(64 * SK), 0, st, a.t_start, a.t_stop, 0, a);
   else

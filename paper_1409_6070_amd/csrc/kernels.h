@@ -4,6 +4,7 @@
 #include <algorithm>
 
 #include "common.h"
+#include "gemm_rules.h"
 
 namespace sscn {
 
@@ -183,12 +184,6 @@ struct GemmArgs {
   // rows, so loads below it may be issued before the device-side count arrives
   int32_t rows_cap;
 };
-
-// Template value of the gather GEMMs for the pooling-forward epilogue (the
-// others: -1 plain, -3 the masked store EPI_STORE_MASK, 0 or 4 the pooling
-// backward with that window count).
-constexpr int POOL_FWD_MODE = -2;
-constexpr int MASK_MODE = -3;
 
 // Byte range of the buffer descriptor through which the bf16 gather GEMM reads
 // its source rows; offsets at or past it read zero (rows without a window

@@ -109,3 +109,25 @@ int main() {
 def test_tiles_are_dealt_once_and_evenly(tmp_path):
     """Every tile once; no workgroup takes more tiles than with one tile after another in plain order."""
     assert int(run_host(tmp_path, TILE_DEAL)) > 100000
+
+
+GEMM_MODES = r"""
+#include "gemm_rules.h"
+#include <cstdio>
+int main() {
+  for (int pool = 0; pool < 2; ++pool)
+    for (int masked = 0; masked < 2; ++masked)
+      for (int ac = -1; ac <= 4; ac += ac < 0 ? 1 : 4)  // no pooling backward, or its window count
+        for (int ks = 1; ks < 4; ++ks)
+          printf("%d %d %d %d %d\n", pool, masked, ac, ks, sscn::gemm_mode(pool, masked, ac >= 0, ac < 0 ? 0 : ac, ks));
+}
+"""
+
+
+def test_split_k_launches_are_plain(tmp_path):
+    """The masked instantiation reads the layer below's tile for its own store; with K split only the
+    reduce stores."""
+    for line in run_host(tmp_path, GEMM_MODES).splitlines():
+        pool, masked, ac, ks, mode = map(int, line.split())
+        want = -2 if pool else -3 if masked and ks == 1 else ac
+        assert mode == want, line
