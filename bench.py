@@ -554,16 +554,16 @@ def traffic_key(kernel_name):
 
 
 # rocprofv3 kernel names of each kernel group of the bench line (template arguments
-# of the direct kernel: <type, waves per tile, epilogue>, 0 and 4 the pooling backward),
+# of the direct kernel: <type, epilogue>, 0 and 4 the pooling backward),
 # and the sources whose hash a counter summary records
 COUNTER_GROUPS = {
     "k_gemm_direct 32x64: input gradient + pooling backward": (
-        r"k_gemm_directIDF16bLi\d+ELi[04]EEE", "gemm_direct.hip epilogue.h pool_route.h ground_tasks.h kernels.h common.h"),
+        r"k_gemm_directIDF16bLi[04]EEE", "gemm_direct.hip epilogue.h gemm_rules.h pool_route.h ground_tasks.h kernels.h common.h"),
     "k_wgrad (all weight gradients, grouped)": (
-        r"k_wgradI|k_wgrad<", "gemm.hip kernels.h common.h ground_tasks.h"),
+        r"k_wgradI|k_wgrad<", "gemm.hip gemm_rules.h kernels.h common.h ground_tasks.h"),
     "k_gemm_gather 64x64: input gradient + pooling backward": (
         r"k_gemm_gatherIDF16bNS_4GCfgIDF16bLi2ELi2ELi2ELi2EEELi[04]EEE|k_gemm_gather<.*, [04]>\(sscn::GemmArgs\)",
-        "gemm.hip epilogue.h pool_route.h ground_tasks.h kernels.h common.h"),
+        "gemm.hip epilogue.h gemm_rules.h pool_route.h ground_tasks.h kernels.h common.h"),
 }
 
 
@@ -681,8 +681,8 @@ def traffic_table(fetch_dir, write_dir, copy_fetch_dir, copy_write_dir, trace_di
     lines += ["", f"Total per step: {tot / 1e6:.1f} MB.", "",
               "Names: `k_gemm_gather` modes -1 plain, -2 with the pooling forward, 0 and 4 with the pooling "
               "backward (4: the children's ground pattern from the rulebook's masks); `GCfg<T, WM, WN, TM, TN>` "
-              "is a (16 WM TM) x (16 WN TN) tile, `k_gemm_direct<T, SK, mode>` the 32 x 64 direct kernel with SK "
-              "waves per tile; the demangler drops the template values of the two routed 64 x 64 "
+              "is a (16 WM TM) x (16 WN TN) tile, `k_gemm_direct<T, mode>` the 32 x 64 direct kernel; "
+              "the demangler drops the template values of the two routed 64 x 64 "
               "`k_gemm_gather` instantiations, which differ in their last value (the mode)."]
     with open(out, "w") as fo:
         fo.write("\n".join(lines) + "\n")

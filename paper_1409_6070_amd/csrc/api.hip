@@ -300,7 +300,6 @@ static const void* zeros(const sscn_net* net) { return net->L[0].X; }
 static void set_plan(const sscn_net* net, GemmArgs& g, const GemmPlan& p, int64_t rows_cap, float* gpart) {
   g.zero = zeros(net);
   g.cfg = p.cfg;
-  g.sk = p.sk;
   g.ksplit = p.ksplit;
   g.part = gpart;
   g.part_rows = (int32_t)rows_cap;

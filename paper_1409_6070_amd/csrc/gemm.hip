@@ -1200,22 +1200,12 @@ GemmPlan plan_gemm(bool bf16, int64_t max_rows, int N, int K, GemmKind kind) {
   const int64_t direct_tiles = ((max_rows + DIRECT_BM - 1) / DIRECT_BM) * ((N + DIRECT_BN - 1) / DIRECT_BN);
   const int64_t most = !bf16 ? 128 : kind == GEMM_ROUTED ? (K <= 320 ? 600 : 256) : kind == GEMM_POOLED ? 256 : 128;
   if (direct_tiles <= most && K <= (!bf16 ? 512 : kind == GEMM_PLAIN ? 1024 : 2048)) {
-    // four waves per tile while the grid stays small (their number also sets the
-    // threads of the epilogue: a window of one over 16 k, 40 tiles: 11.2 us with
-    // one wave), else as many as leave each about four k blocks (32 wide, 16 for
-    // float32)
     GemmPlan p;
     p.cfg = GEMM_DIRECT;
     p.BN = DIRECT_BN;
     p.Npad = (int)round_up(N, DIRECT_BN);
     p.Kpad = (int)round_up(K, 64);
     p.ksplit = 1;
-    const int ksteps = bf16 ? (K + 31) / 32 : (K + 15) / 16;
-    const int64_t tiles = ((max_rows + DIRECT_BM - 1) / DIRECT_BM) * (p.Npad / DIRECT_BN);
-    int sk = 1;
-    while (sk < 4 && sk * 4 < ksteps) sk *= 2;
-    while (sk < 4 && tiles * sk < 4096) sk *= 2;
-    p.sk = sk;
     return p;
   }
   // Tile width: 128 when that pads N no more than 64 does and still gives >= 256

@@ -7,10 +7,13 @@
 // weights Bt[n][k], so each lane issues one 16-byte load per operand and k
 // block -- no LDS staging and no barrier in the K loop.  float32 does the same
 // with 4 consecutive k per lane, one for each of four 16x16x4 steps (k blocks of
-// 16).  A workgroup of SK waves computes one 32 x 64 output tile; wave w sums its
+// 16).  A workgroup of SK = 4 waves computes one 32 x 64 output tile; wave w sums its
 // own contiguous K range, CH k blocks of loads in flight at a time, and the
 // partial sums meet in LDS (in wave order, so the result is deterministic) for
-// the epilogue, which writes 16-byte vectors.
+// the epilogue, which writes 16-byte vectors.  (Four whatever K: the planner sends
+// at most 600 tiles here, fewer than three workgroups a compute unit, and the waves
+// are also the threads of the epilogue: a window of one over 16 k, 40 tiles, 11.2 us
+// with one wave.)
 
 #include "common.h"
 #include "epilogue.h"
@@ -27,6 +30,7 @@ namespace sscn {
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
 constexpr int DIR_AMAX = 9;  // largest window (3x3)
+constexpr int SK = 4;        // waves per workgroup, splitting K
 
 // k / d for 0 <= k < 2^20, 1 <= d < 2^16: float estimate, then exact correction
 __device__ inline int dir_div(int k, int d, float rcp) {
@@ -45,7 +49,7 @@ template <typename T, int AC, bool PRE>
 using PrefetchT = typename std::conditional<PRE, RouteIn<T, AC < 0 ? 0 : AC>, NoPrefetch>::type;
 
 // The sums over the waves of VE columns of one row, in wave order.
-template <int SK, int RP, int VE>
+template <int RP, int VE>
 __device__ inline void wave_sums(float (*red)[DIRECT_BM][RP], int r, int c, float (&s)[VE]) {
 #pragma unroll
   for (int e = 0; e < VE; ++e) s[e] = 0.f;
@@ -59,7 +63,7 @@ __device__ inline void wave_sums(float (*red)[DIRECT_BM][RP], int r, int c, floa
     }
 }
 
-template <typename T, int SK, int RP, int AC, bool PRE, int LDSF>
+template <typename T, int RP, int AC, bool PRE, int LDSF>
 __device__ inline void store_vectors(const GemmArgs& a, float (*red)[DIRECT_BM][RP],
                                      const float (&bias)[Elem<T>::VE], int ce, int m0, int n0, int tm, int rows,
                                      const PrefetchT<T, AC, PRE>& pre) {
@@ -80,7 +84,7 @@ __device__ inline void store_vectors(const GemmArgs& a, float (*red)[DIRECT_BM][
     const int m = m0 + r, n = n0 + ce;
     if (m >= rows || n >= a.out_cols) continue;
     float s[VE];
-    wave_sums<SK, RP, VE>(red, r, ce, s);
+    wave_sums<RP, VE>(red, r, ce, s);
     v4u o;
     v4u y{0u, 0u, 0u, 0u};
     if (a.epi == EPI_STORE_MASK) y = *(const v4u*)((const T*)a.mask + (int64_t)m * a.mask_stride + n);
@@ -115,7 +119,7 @@ __device__ inline void store_vectors(const GemmArgs& a, float (*red)[DIRECT_BM][
 // from slot 0 only) and stages the vector in LDS; then the first maximum over
 // each window's four slots, per channel, goes to the pooling layer with its
 // position.
-template <typename T, int SK, int RP>
+template <typename T, int RP>
 __device__ inline void store_pooled_direct(const GemmArgs& a, float (*red)[DIRECT_BM][RP],
                                            const float (&bias)[Elem<T>::VE], int ce, int m0, int n0, int rows,
                                            const int32_t* Cr) {
@@ -128,7 +132,7 @@ __device__ inline void store_pooled_direct(const GemmArgs& a, float (*red)[DIREC
     const int m = m0 + r, n = n0 + ce;
     if (m >= rows || n >= a.out_cols) continue;
     float s[VE];
-    wave_sums<SK, RP, VE>(red, r, ce, s);
+    wave_sums<RP, VE>(red, r, ce, s);
     v4u o;
 #pragma unroll
     for (int e = 0; e < VE; ++e) ((T*)&o)[e] = Elem<T>::from_f32(epi_value<T>(a, s[e], bias[e]));
@@ -162,7 +166,7 @@ __device__ inline void store_pooled_direct(const GemmArgs& a, float (*red)[DIREC
   }
 }
 
-template <typename T, int SK, int RAC>
+template <typename T, int RAC>
 __global__ void __launch_bounds__(64 * SK) k_gemm_direct(GemmArgs a) {
   constexpr int VE = Elem<T>::VE, KB = 4 * VE;  // k block: four lane groups of VE
   constexpr int TM = DIRECT_BM / 16, TN = DIRECT_BN / 16;
@@ -325,9 +329,9 @@ __global__ void __launch_bounds__(64 * SK) k_gemm_direct(GemmArgs a) {
     __syncthreads();
 
     if constexpr (POOL) {
-      store_pooled_direct<T, SK, RP>(a, red, bias, ce, m0, n0, rows, Cr);
+      store_pooled_direct<T, RP>(a, red, bias, ce, m0, n0, rows, Cr);
     } else if (epi_stores_T(a.epi)) {
-      store_vectors<T, SK, RP, RAC, PRE, LDSF>(a, red, bias, ce, m0, n0, tm, rows, pre);
+      store_vectors<T, RP, RAC, PRE, LDSF>(a, red, bias, ce, m0, n0, tm, rows, pre);
     } else {
       for (int e = tid; e < BM * BN; e += NT) {
         const int r = e / BN, c = e - r * BN;
@@ -343,17 +347,17 @@ __global__ void __launch_bounds__(64 * SK) k_gemm_direct(GemmArgs a) {
   }
 }
 
-template <typename T, int SK>
-static void launch_direct_sk(const GemmArgs& a, int64_t max_rows, hipStream_t st) {
+template <typename T>
+static void launch_direct(const GemmArgs& a, int64_t max_rows, hipStream_t st) {
   const int64_t span = max_rows - a.row_begin;
   const int64_t tiles = ((span + DIRECT_BM - 1) / DIRECT_BM) * (a.Npad / DIRECT_BN);
   const int grid = (int)std::min<int64_t>(std::max<int64_t>(tiles, 1), 2048) + (a.x.kind ? a.x.blocks : 0);
   const int mode = gemm_mode(a.pool_fwd, a.epi == EPI_STORE_MASK, a.route, a.route_ac, a.ksplit);
-  void (*kern)(GemmArgs) = mode == POOL_FWD_MODE ? k_gemm_direct<T, SK, POOL_FWD_MODE>
-                           : mode == MASK_MODE   ? k_gemm_direct<T, SK, MASK_MODE>
-                           : mode == PLAIN_MODE  ? k_gemm_direct<T, SK, PLAIN_MODE>
-                           : mode == 4           ? k_gemm_direct<T, SK, 4>
-                                                 : k_gemm_direct<T, SK, 0>;
+  void (*kern)(GemmArgs) = mode == POOL_FWD_MODE ? k_gemm_direct<T, POOL_FWD_MODE>
+                           : mode == MASK_MODE   ? k_gemm_direct<T, MASK_MODE>
+                           : mode == PLAIN_MODE  ? k_gemm_direct<T, PLAIN_MODE>
+                           : mode == 4           ? k_gemm_direct<T, 4>
+                                                 : k_gemm_direct<T, 0>;
   if (a.t_start || a.t_stop)
     hipExtLaunchKernelGGL(kern, dim3(grid), dim3(64 * SK), 0, st, a.t_start, a.t_stop, 0, a);
   else
@@ -367,19 +371,10 @@ hipError_t launch_gemm_direct(bool bf16, const GemmArgs& a, int64_t max_rows, hi
   if (a.A < 1 || a.A > DIR_AMAX || a.cseg % VE || a.src_stride % VE || a.Npad % DIRECT_BN || a.Kpad % KB ||
       a.Kpad < (a.K + KB - 1) / KB * KB || a.ksplit != 1)
     return hipErrorInvalidValue;
-  switch (a.sk) {
-#define SSCN_DIRECT(SK)                               \
-  if (bf16)                                           \
-    launch_direct_sk<__bf16, SK>(a, max_rows, st);    \
-  else                                                \
-    launch_direct_sk<float, SK>(a, max_rows, st);     \
-  break
-    case 1: SSCN_DIRECT(1);
-    case 2: SSCN_DIRECT(2);
-    case 4: SSCN_DIRECT(4);
-#undef SSCN_DIRECT
-    default: return hipErrorInvalidValue;
-  }
+  if (bf16)
+    launch_direct<__bf16>(a, max_rows, st);
+  else
+    launch_direct<float>(a, max_rows, st);
   return hipGetLastError();
 }
 

@@ -137,7 +137,6 @@ struct GemmArgs {
   int32_t rows_host;
   int32_t row_begin;
   int32_t cfg;        // tile shape (see plan_gemm)
-  int32_t sk;         // GEMM_DIRECT: waves per workgroup, each summing one K range
   int32_t ksplit;     // > 1: K split over workgroups, fp32 partials in part
   float* part;        // [ksplit][part_rows][Npad]
   int32_t part_rows;  // row capacity of part
@@ -200,7 +199,6 @@ struct GemmPlan {
   int Npad = 0;
   int Kpad = 0;
   int ksplit = 1;
-  int sk = 1;  // direct kernel (cfg = GEMM_DIRECT): waves per workgroup splitting K
 };
 
 // cfg value of the direct-operand kernel (gemm_direct.hip): 32 x 64 output
