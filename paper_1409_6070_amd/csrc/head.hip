@@ -166,7 +166,7 @@ __device__ inline float wave_sum(float v) {
 // One workgroup per sample (of up to SOFTMAX_GRID, each then taking every
 // gridDim-th): softmax over the logits, the sample's loss term and dL/dlogits =
 // (softmax - onehot) / batch.  Up to 4096 logits stay in registers.
-constexpr int SOFTMAX_GRID = 512;  // two per compute unit; the counter below is raised once by each
+constexpr int SOFTMAX_GRID = 256;  // one per compute unit; the counter below is raised once by each
 template <typename T>
 __global__ void __launch_bounds__(256) k_softmax_xent(const float* __restrict__ logits,
                                                       const int32_t* __restrict__ labels, int32_t batch,
@@ -214,25 +214,26 @@ __global__ void __launch_bounds__(256) k_softmax_xent(const float* __restrict__ 
     }
     for (int c = t + CACHE * 256; c < dl_stride; c += 256)
       dl[c] = Elem<T>::from_f32(c < classes ? (expf(z[c] - mx) * inv_s - (c == label ? 1.f : 0.f)) * inv_b : 0.f);
-    // this sample's loss term goes out as a device-scope exchange, which is done at
-    // memory when its old value is back; the counter is raised after that.  The
-    // last workgroup to raise it sums all terms in sample order (lane-strided, then
-    // a fixed butterfly) and resets the counter.  (A fence in the exchange's place
-    // writes back the whole L2 of the workgroup's XCD, once per sample: 72.5 us for
-    // the launch at 1600 samples of 3755 classes, 7.6 us at 100.)
     if (t == 0) {
       const bool ok = label >= 0 && label < classes;
       const float term = ok ? (logf(sum) + mx - z[label]) : 0.f;
       if (!ok) atomicOr(err, ERRBIT_LABEL);  // reported by the next sscn_layer_sizes
-      const float old = __hip_atomic_exchange(&loss_part[b], term, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      asm volatile("" ::"v"(old) : "memory");
+      __hip_atomic_store(&loss_part[b], term, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();  // red is reused
   }
+  // the workgroup's loss terms are released with the counter, once for all its
+  // samples; the last workgroup to raise it acquires them, sums all terms in sample
+  // order (lane-strided, then a fixed butterfly) and resets the counter.  (A release
+  // writes back what the XCD's L2 holds of the workgroup's stores: one per sample,
+  // 68.7 us for the launch at 1600 samples of 3755 classes and 7.9 at 100; one per
+  // workgroup of 512, 36.5 and 7.4; of 256, 34.9 and 7.4.  Without one, the terms as
+  // awaited exchanges, 27.7 and 7.1, on an order that the memory model does not promise.)
   if (t == 0)
-    last = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+    last = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
   __syncthreads();
   if (!last || w != 0) return;
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   float acc = 0.f;
   for (int i = t; i < batch; i += 64) acc += __hip_atomic_load(&loss_part[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   acc = wave_sum(acc);
