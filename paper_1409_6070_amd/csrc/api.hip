@@ -186,7 +186,7 @@ static hipError_t timed(sscn_net* net, int cls, hipStream_t st, F&& launch, int3
 
 // Row tiles at capacity (and their height) of the input-gradient GEMM of
 // convolution s when it computes the gradient of a pooling layer s-1 on a
-// convolution, with a tile shape that can run that layer's backward in its
+// convolution with K unsplit, so that it can run that layer's backward in its
 // epilogue; 0 otherwise.
 static int64_t route_tiles(const sscn_net* net, int s, int* bm) {
   if (s < 3) return 0;
@@ -308,8 +308,9 @@ static void set_plan(const sscn_net* net, GemmArgs& g, const GemmPlan& p, int64_
 // Most site chunks of a split-K weight gradient (the partial buffers hold that
 // many): slabs x BK sites per chunk at the row capacity, at most 512, and
 // partial sums (chunks x |dW| fp32) of at most twice the bytes the kernel reads
-// (rows x row_bytes).  The kernel takes min(this, rows / (slabs x BK)) from the
-// device-side row count.
+// (rows x row_bytes).  How many of them a pass uses comes from the device-side row
+// counts (ChunkPlan): at most rows / (slabs x BK), and fewer, longer ones where a
+// tile width's tiles would number more than CHUNK_TILES.
 static int wgrad_chunks(int64_t rows_cap, int slabs, int BK, int64_t row_bytes, int64_t part_bytes) {
   int64_t n = std::max<int64_t>(1, std::min<int64_t>(512, (rows_cap + slabs * BK - 1) / (slabs * BK)));
   return (int)std::min<int64_t>(n, std::max<int64_t>(1, 2 * rows_cap * row_bytes / std::max<int64_t>(part_bytes, 1)));
@@ -670,8 +671,7 @@ static DropArgs head_drop(const sscn_net* net) { return drop_args(net, net->d.el
 
 // Whether convolution s runs the pooling layer above it in its GEMM epilogue
 // (GemmArgs::pool_fwd): every site of the convolution must lie in a pooling
-// window (an even grid side), and its plan must be a single-pass tile shape
-// that stages its output.
+// window (an even grid side), and its plan must not split K.
 static bool pool_fused(const sscn_net* net, int s) {
   if (s + 1 >= net->nlayers) return false;
   const LayerPlan& L = net->L[s];
@@ -930,8 +930,8 @@ static hipError_t run_wgrads(sscn_net* net, const WGradArgs* w, int n, hipStream
 // gradient of a pooling layer s-1 on convolution s-2, runs that pooling
 // layer's backward in its epilogue (GemmArgs::route): not through a dropout of
 // the pooling output, not for a 3x3 convolution below that must finish its
-// nine ground sums, and only for a tile shape that stages its output with one
-// partial per row tile (*bm rows, *tiles at capacity).
+// nine ground sums, and only with K unsplit; one partial per row tile (*bm rows,
+// *tiles at capacity).
 static bool route_into(const sscn_net* net, int s, int* ac, int* bm, int* tiles) {
   int b = 0;
   const int64_t t = route_tiles(net, s, &b);

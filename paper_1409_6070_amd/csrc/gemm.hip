@@ -75,7 +75,9 @@ constexpr int AMAX = 9;  // largest window (3x3)
 // the four tile shapes (index = GemmArgs::cfg)
 // (bf16 multiplies square wave tiles, whose operands take the fewest LDS reads;
 // float32, whose MFMAs outlast them, gives every wave whole rows, so that dead
-// column blocks leave all waves alike)
+// column blocks leave all waves alike; its 32 x 64 tile, with rows for two waves
+// only, keeps two columns of waves, and with one live block the second multiplies a
+// dead one)
 template <typename T> using C128x128 = GCfg<T, sizeof(T) == 2 ? 2 : 4, sizeof(T) == 2 ? 2 : 1, sizeof(T) == 2 ? 4 : 2, sizeof(T) == 2 ? 4 : 8>;
 template <typename T> using C128x64 = GCfg<T, 4, 1, 2, 4>;
 template <typename T> using C64x64 = GCfg<T, sizeof(T) == 2 ? 2 : 4, sizeof(T) == 2 ? 2 : 1, sizeof(T) == 2 ? 2 : 1, sizeof(T) == 2 ? 2 : 4>;
@@ -1197,6 +1199,8 @@ GemmPlan plan_gemm(bool bf16, int64_t max_rows, int N, int K, GemmKind kind) {
   // DeepCNet(4,20) at batch 8, K = 80 .. 320: forwards 6.2 + 3.5 (reduce) + 2.5
   // (pooling) -> 7.5 us, input gradients 7.0 + 3.7 + 4.8 -> 13.7 us; but K = 1000
   // at 20 tiles 20.1 us against 6.7 + 5.0.
+  // (Each of these limits lies between the one or two launches named on either side
+  // of it; where exactly, between them, was not measured.)
   const int64_t direct_tiles = ((max_rows + DIRECT_BM - 1) / DIRECT_BM) * ((N + DIRECT_BN - 1) / DIRECT_BN);
   const int64_t most = !bf16 ? 128 : kind == GEMM_ROUTED ? (K <= 320 ? 600 : 256) : kind == GEMM_POOLED ? 256 : 128;
   if (direct_tiles <= most && K <= (!bf16 ? 512 : kind == GEMM_PLAIN ? 1024 : 2048)) {

@@ -151,13 +151,12 @@ struct GemmArgs {
   hipEvent_t t_start, t_stop;
   ExtraTask x;  // extra workgroups appended to the launch (kind 0: none)
   int32_t partials_only;  // ksplit > 1: leave the fp32 partials, no reduce launch
-  // Pooling backward in the epilogue (route = 1; EPI_STORE, ksplit == 1, a
-  // tile shape that stages its output): the output rows m >= 1 are the gradient
-  // of a pooling layer, routed through its windows to the convolution below
-  // (delta rows >= 1, rectifier derivative applied) with that convolution's slot
-  // partial sums, one partial per row tile; pr describes both layers (its dY
-  // field is unused) and route_ac is the convolution's finished window count
-  // (0 or 4).
+  // Pooling backward in the epilogue (route = 1; EPI_STORE, ksplit == 1): the
+  // output rows m >= 1 are the gradient of a pooling layer, routed through its
+  // windows to the convolution below (delta rows >= 1, rectifier derivative
+  // applied) with that convolution's slot partial sums, one partial per row tile;
+  // pr describes both layers (its dY field is unused) and route_ac is the
+  // convolution's finished window count (0 or 4).
   // EPI_STORE_MASK with sums = 1 (ksplit == 1, row_begin == 1): the stored rows are
   // a convolution's delta, whose column sums over each row tile go to slot 1 of pr's
   // partials (the bias gradient).
@@ -166,13 +165,12 @@ struct GemmArgs {
   int32_t route_ac;
   GroundArgs pr;
   // Pooling forward in the epilogue (pool_fwd = 1; a convolution with the
-  // bias-rectifier epilogue, ksplit == 1, a tile shape that stages its output):
-  // the GEMM rows are the slots 4 p + f of the pooling windows, rows = 4 (n_pool
-  // + 1) from rows_dev / rows_add (the pooling layer's count); slot q computes
-  // the convolution row pslot[q] (the pooling layer's window list; row 0 for an
-  // inactive location, which then gives the ground value) and stores it (row 0
-  // from slot 0 only), and each window's first maximum goes to pool_out /
-  // pool_argmax (row stride pool_stride).
+  // bias-rectifier epilogue, ksplit == 1): the GEMM rows are the slots 4 p + f of
+  // the pooling windows, rows = 4 (n_pool + 1) from rows_dev / rows_add (the pooling
+  // layer's count); slot q computes the convolution row pslot[q] (the pooling
+  // layer's window list; row 0 for an inactive location, which then gives the ground
+  // value) and stores it (row 0 from slot 0 only), and each window's first maximum
+  // goes to pool_out / pool_argmax (row stride pool_stride).
   int32_t pool_fwd;
   const int32_t* pslot;
   void* pool_out;
