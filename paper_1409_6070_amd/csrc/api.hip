@@ -79,7 +79,8 @@ struct sscn_net {
   ParamPlan P[MAX_LAYERS];
   int dl_stride;  // dlogits row stride (elements)
   int pool_parts;
-  int wgrad_slabs[2];  // slabs of sites per weight-gradient chunk, 128- and 64-wide tiles
+  int wgrad_slabs[2];  // slabs of sites per weight-gradient chunk as planned, 128- and 64-wide tiles
+  int wgrad_div;       // the standard chunk length over that
   // global workspace pointers
   int32_t* counts;
   int32_t* err;   // [4]: the input-error word, then completion counters (zeroed by every rulebook build,
@@ -309,8 +310,8 @@ static void set_plan(const sscn_net* net, GemmArgs& g, const GemmPlan& p, int64_
 // many): slabs x BK sites per chunk at the row capacity, at most 512, and
 // partial sums (chunks x |dW| fp32) of at most twice the bytes the kernel reads
 // (rows x row_bytes).  How many of them a pass uses comes from the device-side row
-// counts (ChunkPlan): at most rows / (slabs x BK), and fewer, longer ones where a
-// tile width's tiles would number more than CHUNK_TILES.
+// counts (ChunkPlan): at most rows / (slabs x BK), and fewer, longer ones where these
+// would make more tiles than pay.
 static int wgrad_chunks(int64_t rows_cap, int slabs, int BK, int64_t row_bytes, int64_t part_bytes) {
   int64_t n = std::max<int64_t>(1, std::min<int64_t>(512, (rows_cap + slabs * BK - 1) / (slabs * BK)));
   return (int)std::min<int64_t>(n, std::max<int64_t>(1, 2 * rows_cap * row_bytes / std::max<int64_t>(part_bytes, 1)));
@@ -464,9 +465,11 @@ sscn_status sscn_net_create(const sscn_net_desc* desc, sscn_net** out) {
   // Site chunks of the weight gradients: 8 slabs of sites each (128-wide tiles)
   // or 12 (64-wide), and a half or a quarter of that while the convolutions' tiles
   // at the row bound number fewer than 1024: a small network's few chunks would
-  // each be a long serial loop on a mostly idle chip (DeepCNet(4,20), float32,
-  // batch 8: 88 tiles, 41 us; bf16, batch 100: 372 tiles, 32 us).
+  // each be a long serial loop on a mostly idle chip.  (The plan bounds the partial
+  // sums' buffer; each pass takes the planned length or twice or four times that, by
+  // its own rows: chunk_multiple.)
   for (int div = 1; div <= 4; div *= 2) {
+    net->wgrad_div = div;
     net->wgrad_slabs[0] = WG_SLABS_128 / div;
     net->wgrad_slabs[1] = WG_SLABS_64 / div;
     int64_t tiles = 0;
@@ -1066,6 +1069,7 @@ sscn_status sscn_forward(sscn_net* net, const void* d_feats, const void* const* 
       c.tiles = (P.Mpad_w / WG_BM) * (P.Npad_w / P.bn_w);
     }
     pa.ch.n = net->nconv;
+    pa.ch.div = net->wgrad_div;
   }
   if (timed(net, SSCN_KC_HEAD, st, [&] { return launch_pack_all(net->bf16, pa, st); }) != hipSuccess)
     return SSCN_ERR_HIP;

@@ -58,4 +58,25 @@ constexpr inline int gemm_mode(bool pool_fwd, bool masked, bool route, int route
   return route ? (route_ac == 4 ? 4 : 0) : PLAIN_MODE;
 }
 
+// Site chunks of the weight gradients.  A network with few tiles plans chunks of a
+// half or a quarter (div 2 or 4) of the standard length; how long a pass makes them
+// is decided from the tiles that its own rows give at each length (convolutions of
+// both tile widths together): the shortest of a quarter with at most 512 tiles, a half
+// with at most 700, and the standard length.  Below that a launch leaves compute units
+// idle and a chunk is a serial loop; above, shorter chunks only multiply the partial
+// sums.  Weight gradients and their reduce, in us at the standard length / a half / a
+// quarter, with the tiles: DeepCNet(4,20), float32, batch 8 (32 / 57 / 108 tiles) 45.7 /
+// 36.1 / 25.8; from paths, bf16, batch 100 (83 / 158 / 310) 36.0 / 28.1 / 28.2;
+// DeepCNet(5,64), batch 7 (147 / 210 / 338) 36.1 / 27.7 / 26.3; DeepCNet(4,77), batch 16
+// (259 / 388 / 686) 35.3 / 28.7 / 32.1; DeepCNiN(4,40), batch 100 (362 / 691 / 1346)
+// 42.3 / 36.9 / 45.8; DeepCNet(3,50), batch 300 (322 / 630 / 1237) 39.9 / 40.6 / 51.4;
+// DeepCNet(4,100), batch 30 (428 / 769 / 1416) 38.6 / 40.3 / 46.5; DeepCNiN(2,60), batch
+// 1500 (384 / 766 / 1273) 59.2 / 61.8 / 69.8.
+// Returns the multiple (1 .. div) of the planned length; tiles[i]: at a multiple of 2^i.
+constexpr inline int chunk_multiple(int div, int64_t const (&tiles)[3]) {
+  if (div == 4 && tiles[0] <= 512) return 1;
+  if (div >= 2 && tiles[div == 4 ? 1 : 0] <= 700) return div / 2;
+  return div;
+}
+
 }  // namespace sscn

@@ -51,19 +51,26 @@ __global__ void __launch_bounds__(256) k_gather_dfeats(const T* __restrict__ gra
 
 // ChunkPlan, by one workgroup: a thread per layer.
 __device__ inline void plan_chunks(const ChunkPlan& p) {
-  __shared__ int tiles[2];
-  if (threadIdx.x < 2) tiles[threadIdx.x] = 0;
+  __shared__ int tiles[3][2];  // at multiples 1, 2, 4 of the planned length, by tile width
+  if (threadIdx.x < 6) tiles[threadIdx.x >> 1][threadIdx.x & 1] = 0;
   __syncthreads();
   const int l = threadIdx.x;
   int rows = 0, cfg = 0;
   if (l < p.n) {
     rows = p.counts[p.L[l].layer] + 1;
     cfg = p.L[l].cfg;
-    atomicAdd(&tiles[cfg], min(p.L[l].nchunks, (rows + p.L[l].sites - 1) / p.L[l].sites) * p.L[l].tiles);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const int per = p.L[l].sites << i;
+      atomicAdd(&tiles[i][cfg], min(p.L[l].nchunks, (rows + per - 1) / per) * p.L[l].tiles);
+    }
   }
   __syncthreads();
   if (l >= p.n) return;
-  const int64_t per = (int64_t)p.L[l].sites * max(1, (tiles[cfg] + CHUNK_TILES - 1) / CHUNK_TILES);
+  const int m = chunk_multiple(p.div, {(int64_t)tiles[0][0] + tiles[0][1], (int64_t)tiles[1][0] + tiles[1][1],
+                                       (int64_t)tiles[2][0] + tiles[2][1]});
+  const int most = tiles[m == 4 ? 2 : m == 2 ? 1 : 0][cfg];
+  const int64_t per = (int64_t)p.L[l].sites * m * max(1, (most + CHUNK_TILES - 1) / CHUNK_TILES);
   p.nch[l] = max(1, min(p.L[l].nchunks, (int)((rows + per - 1) / per)));
 }
 

@@ -330,8 +330,9 @@ struct ScatterArgs {
   int32_t blocks;  // workgroups given to it (0: no scatter)
 };
 // The site chunks of the weight gradients, from the device-side row counts: per
-// layer, `sites` a chunk as planned, and the same multiple of that for all layers
-// of a tile width that brings their tiles down to CHUNK_TILES (two to three rounds
+// layer, `sites` a chunk as planned or a multiple of that up to `div` (chunk_multiple),
+// and the same multiple of that again for all layers of a tile width that brings their
+// tiles down to CHUNK_TILES (two to three rounds
 // of resident workgroups; more tiles only multiply the partial sums, which
 // DeepCNet(5,50) at batch 1600 wrote and read back 314 MB of: weight gradients and
 // reduce 537 -> 450 us); at most the planned chunk count.  Worked out once a pass,
@@ -339,6 +340,7 @@ struct ScatterArgs {
 constexpr int CHUNK_TILES = 1536;
 struct ChunkPlan {
   int32_t n;
+  int32_t div;            // the standard chunk length over the planned one: 1, 2 or 4
   const int32_t* counts;  // active sites per layer
   int32_t* nch;           // [n], the result
   struct {

@@ -140,3 +140,21 @@ def test_first_layers_final_pass_without_dfeats(case, dtype):
     pair = Pair(ell, k, 1, ncls, batch, coords, feats, Ws, bs, random_labels(batch, ncls, 80 + k), dtype, arch=arch,
                 want_dfeats=False).run_gpu()
     check_values(pair)
+
+
+# Weight gradients whose pass takes another chunk length than the plan's shortest.  dtype, ell, k, batch,
+# density; tiles at a quarter / a half of the standard length and at it: a half of a network planned at
+# quarters (612 and 412 tiles), the standard length of one planned at quarters (1324 / 738 / 375) and at
+# halves (1324 / 738), the quarter (501)
+CHUNKED = [("bf16", 2, 60, 1500, 0.3), ("f32", 2, 60, 500, 0.3), ("bf16", 3, 50, 300, 0.2), ("f32", 3, 50, 300, 0.2),
+           ("f32", 2, 60, 300, 0.3)]
+
+
+@pytest.mark.parametrize("case", CHUNKED, ids=[f"{c[0]}_l{c[1]}k{c[2]}_b{c[3]}" for c in CHUNKED])
+def test_weight_gradients_of_every_chunk_length(case):
+    dtype, ell, k, batch, p = case
+    coords, feats = _sparse_case(970 + k, ell, batch, p, 1)
+    log(f"[chunks] {case} n={len(coords)}")
+    Ws, bs = he_params(ell, k, 1, 10, 90 + k)
+    pair = Pair(ell, k, 1, 10, batch, coords, feats, Ws, bs, random_labels(batch, 10, 95 + k), dtype).run_gpu()
+    check_values(pair)

@@ -131,3 +131,29 @@ def test_split_k_launches_are_plain(tmp_path):
         pool, masked, ac, ks, mode = map(int, line.split())
         want = -2 if pool else -3 if masked and ks == 1 else ac
         assert mode == want, line
+
+
+CHUNKS = r"""
+#include "gemm_rules.h"
+#include <cstdio>
+int main() {
+  const long long at[][3] = {{108, 57, 32}, {310, 158, 83}, {338, 210, 147}, {512, 300, 160}, {513, 300, 160}, {686, 388, 259},
+                             {1346, 691, 362}, {1400, 700, 370}, {1402, 701, 370}, {1416, 769, 428}, {1273, 766, 384}};
+  for (auto& t : at)
+    for (int div = 1; div <= 4; div *= 2) {  // planned lengths: the last `levels` of (quarter, half, standard)
+      const int skip = div == 4 ? 0 : div == 2 ? 1 : 2;
+      long tiles[3] = {0, 0, 0};
+      for (int i = 0; i + skip < 3; ++i) tiles[i] = t[i + skip];
+      printf("%lld %lld %d %d\n", t[0], t[1], div, sscn::chunk_multiple(div, tiles));
+    }
+}
+"""
+
+
+def test_chunks_are_as_short_as_the_passes_own_tiles_allow(tmp_path):
+    """A quarter of the standard length with at most 512 tiles, else a half with at most 700, else the
+    standard one; never shorter than planned."""
+    for line in run_host(tmp_path, CHUNKS).splitlines():
+        quarter, half, div, got = map(int, line.split())
+        want = 4 if quarter <= 512 and div == 4 else 2 if half <= 700 and div >= 2 else 1  # parts of the standard length
+        assert div // got == want and div % got == 0, line
