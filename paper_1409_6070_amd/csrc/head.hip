@@ -173,7 +173,7 @@ __device__ inline float wave_sum(float v) {
 // One workgroup per sample (of up to SOFTMAX_GRID, each then taking every
 // gridDim-th): softmax over the logits, the sample's loss term and dL/dlogits =
 // (softmax - onehot) / batch.  Up to 4096 logits stay in registers.
-constexpr int SOFTMAX_GRID = 256;  // one per compute unit; the counter below is raised once by each
+constexpr int SOFTMAX_GRID = 512;  // two per compute unit; the counter below is raised once by each
 template <typename T>
 __global__ void __launch_bounds__(256) k_softmax_xent(const float* __restrict__ logits,
                                                       const int32_t* __restrict__ labels, int32_t batch,
@@ -232,10 +232,11 @@ __global__ void __launch_bounds__(256) k_softmax_xent(const float* __restrict__ 
   // the workgroup's loss terms are released with the counter, once for all its
   // samples; the last workgroup to raise it acquires them, sums all terms in sample
   // order (lane-strided, then a fixed butterfly) and resets the counter.  (A release
-  // writes back what the XCD's L2 holds of the workgroup's stores: one per sample,
-  // 68.7 us for the launch at 1600 samples of 3755 classes and 7.9 at 100; one per
-  // workgroup of 512, 36.5 and 7.4; of 256, 34.9 and 7.4.  Without one, the terms as
-  // awaited exchanges, 27.7 and 7.1, on an order that the memory model does not promise.)
+  // writes back what the XCD's L2 holds of the workgroup's stores, and they queue: one
+  // per sample 63.2 us for the launch at 1600 samples of 3755 classes, 139.5 at 6000 of
+  // 10, 12.4 at 300 of 3755; one per workgroup of 512 31.5, 56.5, 11.6, of 256 32.2,
+  // 75.1, 13.0, of 1024 40.0, 51.0, 11.4.  Without one, the terms as awaited exchanges,
+  // 24.3, 56.2, 9.5, on an order that the memory model does not promise.)
   if (t == 0)
     last = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
   __syncthreads();

@@ -50,7 +50,7 @@ def test_window_lists_of_large_batches(batch, p):
     pair = Pair(ell, k, 1, ncls, batch, coords, feats, Ws, bs, random_labels(batch, ncls, 8), "f32")
     pair.run_gpu()
     check_structure(pair)
-    # the loss is the sum of every sample's term, several samples to a workgroup above 256
+    # the loss is the sum of every sample's term, several samples to a workgroup above 512
     np.testing.assert_allclose(pair.loss, pair.o.loss, rtol=1e-5)
 
 
