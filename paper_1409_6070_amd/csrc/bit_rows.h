@@ -40,14 +40,16 @@ constexpr inline void dilate_row(uint64_t* row, int nw, int a, int r) {
   }
 }
 
-// A row of NW <= 3 words in registers, r <= 64 NW: no shift is longer than a word
-// (they go 1, 2, .. 64, and the last covers what is left of r).  In the row buffer
-// each word of each round was a dependent chain through LDS, which cost more than
-// the per-bit tests on grids of up to 128 columns: the whole bitmap launch at
-// batch 1600, 96 x 96 grids, 36.8 us by tests, 37.9 in LDS, 33.0 like this; 24 x 24
-// 17.0, 18.5, 15.6; batch 64, 192 x 192 25.9, 12.3, 10.8.
+// A row of NW <= 3 words in registers, r <= 64 NW, of which n result bits are wanted:
+// no shift is longer than a word (they go 1, 2, .. 64, and the last covers what is
+// left of r).  Up to eight bits are picked one by one, about six operations each
+// against thirty for each round of packing a word.  (In the row buffer each word of
+// each round was a dependent chain through LDS.  The whole bitmap launch by per-bit
+// tests / in the row buffer / in registers: 96 x 96 grids at batch 1600 36.7 / 37.8 /
+// 33.3 us, at batch 100 10.1 / 9.7 / 8.3; 192 x 192 at batch 64 25.9 / 12.4 / 10.9;
+// 48 x 48 at batch 8 7.0 / 7.3 / 6.2; 12 x 12 at batch 2 4.8 / 6.2 / 5.6.)
 template <int NW>
-constexpr inline void dilate_words(uint64_t (&row)[NW], int a, int r) {
+constexpr inline void dilate_words(uint64_t (&row)[NW], int a, int r, int n) {
   static_assert(NW >= 1 && NW <= 3, "no shift above 64");
   for (int len = 1; len < r;) {
     const int sh = len < r - len ? len : r - len;
@@ -57,6 +59,20 @@ constexpr inline void dilate_words(uint64_t (&row)[NW], int a, int r) {
       row[w] |= sh < 64 ? (row[w] >> sh) | (hi << (64 - sh)) : hi;
     }
     len += sh;
+  }
+  if (a > 1 && n <= 8) {
+    uint64_t bits = 0;
+    for (int X = 0; X < n; ++X) {
+      const int at = a * X;
+      uint64_t v = row[0];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) v = at >= 64 * w ? row[w] : v;
+      bits |= ((v >> (at & 63)) & 1ull) << X;
+    }
+    row[0] = bits;
+#pragma unroll
+    for (int w = 1; w < NW; ++w) row[w] = 0ull;
+    return;
   }
   int nw = NW;
   for (int st = a; st > 1; st >>= 1) {

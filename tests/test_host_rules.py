@@ -28,10 +28,10 @@ BIT_ROWS = r"""
 using namespace sscn;
 typedef std::vector<uint64_t> Row;
 static bool bit(const Row& r, int i) { return r[i >> 6] >> (i & 63) & 1; }
-template <int NW> static void words(Row& r, int a, int reach) {
+template <int NW> static void words(Row& r, int a, int reach, int n) {
   uint64_t v[NW];
   for (int w = 0; w < NW; ++w) v[w] = r[w];
-  dilate_words(v, a, reach);
+  dilate_words(v, a, reach, n);
   for (int w = 0; w < NW; ++w) r[w] = v[w];
 }
 int main() {
@@ -49,9 +49,9 @@ int main() {
           for (int kind = 0; kind < (nw <= 3 ? 2 : 1); ++kind) {
             Row got = in;
             if (kind == 0) dilate_row(got.data(), nw, a, r);
-            else if (nw == 1) words<1>(got, a, r);
-            else if (nw == 2) words<2>(got, a, r);
-            else words<3>(got, a, r);
+            else if (nw == 1) words<1>(got, a, r, So);
+            else if (nw == 2) words<2>(got, a, r, So);
+            else words<3>(got, a, r, So);
             for (int X = 0; X < So; ++X) {
               bool any = false;
               for (int i = a * X; i < a * X + r; ++i) any = any || bit(in, i);
